@@ -298,7 +298,6 @@ struct Band2D {
     double r;
     int32_t bc_top, bc_bot;
     int32_t hw;
-    int32_t aligned;       // every row of in/out/halos starts 16-byte aligned
     // Rescaled update (set_rate_2d for the pass's depth): period > 0 selects it.
     int32_t period;        // levels between rescales
     double beta;           // r / (1 - 4r)

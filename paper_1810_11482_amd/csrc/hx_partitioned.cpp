@@ -99,7 +99,6 @@ hx_status run_bands_batched(Ctx* c, const hx_partitioned_desc* d, hx_event gate,
     }
     const bool give = node_events != nullptr;
     int node = 0;
-    auto al = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; };
     // On an error, drop our references (node events handed to the caller
     // stay the caller's); what was already queued still runs.
     bool first_pass = true;
@@ -157,8 +156,6 @@ hx_status run_bands_batched(Ctx* c, const hx_partitioned_desc* d, hx_event gate,
                 bd.out = pout;
                 bd.halo_top = ptop;
                 bd.halo_bot = pbot;
-                bd.aligned = (d->nx % vn == 0) && al(pin) && al(pout) && (!ptop || al(ptop)) &&
-                             (!pbot || al(pbot));
                 bands.push_back(bd);
             }
             hx_event ev = 0;

@@ -217,9 +217,6 @@ static hx_status launch_2d(Ctx* c, const hx_stencil_args* a, const hx_event* dep
                 return c->fail(HX_ERR_ARG, "tmp overlaps another operand");
         acc.push_back(ac);
     }
-    auto al = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; };
-    const bool aligned = (nx % vn == 0) && al(pin) && al(pout) && (!ptmp || al(ptmp)) &&
-                         (!ptop || al(ptop)) && (!pbot || al(pbot));
     Band2D band{};
     band.nx = nx;
     band.ny = ny;
@@ -229,7 +226,6 @@ static hx_status launch_2d(Ctx* c, const hx_stencil_args* a, const hx_event* dep
     band.hw = a->halo_width;
     band.halo_top = ptop;
     band.halo_bot = pbot;
-    band.aligned = aligned ? 1 : 0;
     std::string what = "stencil2d " + std::to_string(ny) + "x" + std::to_string(nx) +
                        " steps=" + std::to_string(a->steps);
     return c->submit(
