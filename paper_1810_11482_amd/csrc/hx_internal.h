@@ -343,6 +343,28 @@ hipError_t launch_stencil2d(int dtype, const Band2D& b, const Geom2D& g, hipStre
 constexpr int kMaxBands = 16;
 hipError_t launch_stencil2d_bands(int dtype, const Band2D* bands, int n, const Geom2D& g,
                                   hipStream_t stream);
+// The same pass in the tile form (hx_tile2d.hip): a workgroup of g.wpg waves
+// holds 256 columns x wpg * g.rows rows in registers (g.rows = 4 rows per wave
+// with 2 to 16 waves, or 8 with 2 to 8), 1 <= g.steps <= 31 and
+// 2 g.steps < wpg * rows.  The same bits as the streaming form at the same
+// depth.
+hipError_t launch_tile2d_bands(int dtype, const Band2D* bands, int n, const Geom2D& g,
+                               hipStream_t stream);
+// The form and geometry of a pass of `depth` steps over n bands when the
+// caller leaves them to the library (hx_tile2d.hip says where the lines lie);
+// *us receives the pass's modelled time.  Any depth the tile form takes.
+struct Form2D {
+    bool tile;
+    Geom2D g;
+};
+Form2D choose_form2d(int dtype, int64_t nx, const int64_t* ny, int n, int depth, double* us);
+// Pass depths of a run of `steps` steps over one grid, in the library's choice.
+std::vector<int> choose_depths2d(int dtype, int64_t nx, int64_t ny, int steps);
+inline hipError_t launch_form2d(int dtype, const Band2D* bands, int n, const Form2D& f,
+                                hipStream_t stream) {
+    return f.tile ? launch_tile2d_bands(dtype, bands, n, f.g, stream)
+                  : launch_stencil2d_bands(dtype, bands, n, f.g, stream);
+}
 
 // One variable-coefficient step (forward: out = A u; adjoint: out = A^T lam
 // and gacc += the step's conductivity gradient) on an ny x nx grid.

@@ -72,6 +72,8 @@ hx_status run_bands_batched(Ctx* c, const hx_partitioned_desc* d, hx_event gate,
     const int dt = d->dtype == HX_F64 ? 1 : 0;
     const int64_t es = dt ? 8 : 4;
     const int vn = dt ? 2 : 4;
+    // the library's own form and geometry, unless some of it is given
+    const bool choose = !d->cells_per_lane && !d->rows_per_block && !d->waves_per_group;
     Geom2D g;
     g.cpl = d->cells_per_lane ? d->cells_per_lane : 4;
     g.rows = d->rows_per_block ? d->rows_per_block : 128;
@@ -112,9 +114,9 @@ hx_status run_bands_batched(Ctx* c, const hx_partitioned_desc* d, hx_event gate,
     for (size_t b = 0; b < plan.size(); ++b) {
         const int depth = plan[b];
         const bool src_a = (b % 2 == 0);
-        Geom2D gg = g;
-        gg.steps = depth;
-        gg.halo = std::max(vn, (depth + vn - 1) / vn * vn);
+        Form2D f{false, g};
+        f.g.steps = depth;
+        f.g.halo = std::max(vn, (depth + vn - 1) / vn * vn);
         for (int gi = 0; gi < groups; ++gi) {
             const int p0 = gi * kMaxBands, p1 = std::min(P, p0 + kMaxBands);
             std::vector<Band2D> bands;
@@ -160,11 +162,13 @@ hx_status run_bands_batched(Ctx* c, const hx_partitioned_desc* d, hx_event gate,
             }
             hx_event ev = 0;
             const int dtype = dt;
+            double us;
+            if (choose) f = choose_form2d(dt, d->nx, d->sizes + p0, p1 - p0, depth, &us);
             hx_status s = c->submit(
                 SC_COMPUTE, prev.data(), (int)prev.size(), acc,
                 "stencil2d batched pass of " + std::to_string(bands.size()) + " bands",
-                [bands, gg, dtype](hipStream_t st) -> hipError_t {
-                    return launch_stencil2d_bands(dtype, bands.data(), (int)bands.size(), gg, st);
+                [bands, f, dtype](hipStream_t st) -> hipError_t {
+                    return launch_form2d(dtype, bands.data(), (int)bands.size(), f, st);
                 },
                 &ev);
             if (s) return unwind(s);

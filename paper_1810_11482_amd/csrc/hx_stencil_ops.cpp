@@ -164,7 +164,10 @@ static hx_status launch_2d(Ctx* c, const hx_stencil_args* a, const hx_event* dep
     acc.push_back(ac);
 
     TunedGeom tg;
-    const bool tuned = tune_lookup(tune_key_2d(dt, ny, nx, a->steps), &tg);
+    const bool tuned = tune_lookup(tune_key_2d(dt, ny, nx, a->steps), &tg) && tg.mode == 0;
+    // the library's own form and geometry of each pass, unless some of it is
+    // given or tuned
+    const bool choose = !tuned && !a->cells_per_lane && !a->waves_per_group && !a->rows_per_block;
     Geom2D g{};
     g.cpl = a->cells_per_lane ? a->cells_per_lane : (tuned && tg.cpl ? tg.cpl : 4);
     g.wpg = a->waves_per_group ? a->waves_per_group : (tuned && tg.wpg ? tg.wpg : 4);
@@ -206,8 +209,12 @@ static hx_status launch_2d(Ctx* c, const hx_stencil_args* a, const hx_event* dep
         }
         if (plan.empty()) plan.push_back(0);
     }
+    // (a run of more than one pass of time_block steps, or of 8, needs tmp
+    // whatever depths are chosen)
+    const bool need_tmp = plan.size() > 1;
+    if (choose && !a->time_block && need_tmp) plan = choose_depths2d(dt, nx, ny, a->steps);
     const int passes = (int)plan.size();
-    if (passes > 1) {
+    if (need_tmp) {
         if (a->tmp == 0)
             return c->fail(HX_ERR_ARG, "a run of more than one pass needs a tmp buffer");
         s = resolve_range(c, a->tmp, a->tmp_offset, bytes, &ptmp, &ac, true);
@@ -242,10 +249,12 @@ static hx_status launch_2d(Ctx* c, const hx_stencil_args* a, const hx_event* dep
                     hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, st);
                     if (e != hipSuccess) return e;
                 } else {
-                    Geom2D gg = g;
-                    gg.steps = plan[p];
-                    gg.halo = std::max(vn, round_up(plan[p], vn));
-                    hipError_t e = launch_stencil2d(dt, bb, gg, st);
+                    Form2D f{false, g};
+                    f.g.steps = plan[p];
+                    f.g.halo = std::max(vn, round_up(plan[p], vn));
+                    double us;
+                    if (choose) f = choose_form2d(dt, bb.nx, &bb.ny, 1, plan[p], &us);
+                    hipError_t e = launch_form2d(dt, &bb, 1, f, st);
                     if (e != hipSuccess) return e;
                 }
                 src = dst;

@@ -92,11 +92,17 @@ void tune_store(const TuneKey& k, const TunedGeom& g) {
     g_tune[k.s] = g;
 }
 
+void tune_erase(const TuneKey& k) {
+    std::lock_guard<std::mutex> lk(g_tune_mu);
+    load_file_locked();
+    g_tune.erase(k.s);
+}
+
 Geom1D default_geom_1d(Ctx* c, const TuneKey& k) {
     (void)c;
     TunedGeom t;
     Geom1D g;
-    if (tune_lookup(k, &t) && t.cpl) {
+    if (tune_lookup(k, &t) && t.cpl && t.mode == 0) {
         g.cpl = t.cpl;
         g.steps = t.steps;
         g.wpg = t.wpg ? t.wpg : 4;
@@ -242,6 +248,13 @@ extern "C" hx_status hx_tune_stencil(hx_ctx ctx, const hx_stencil_args* args, in
     g.rows = best->rows_per_block;
     const TuneKey k = two_d ? tune_key_2d(args->dtype, args->ny, args->nx, args->steps)
                             : tune_key_1d(args->dtype, args->nx, args->steps, ghost);
+    // *best is the fastest geometry that can be named; a launch that names
+    // none keeps the library's own choice if that is faster still
+    tune_erase(k);
+    hx_stencil_args own = *args;
+    own.cells_per_lane = own.time_block = own.waves_per_group = own.rows_per_block = 0;
+    const double t_own = time_stencil(ctx, own, 2);
+    g.mode = t_own > 0 && t_own < best_t ? 1 : 0;
     tune_store(k, g);
     return HX_OK;
 }

@@ -23,7 +23,9 @@ struct TunedGeom {
     int rows = 0;      // 2D rows per wave
     int grid = 0;      // batched: waves per CU
     int mode = 0;      // batched: chosen hx_batch_form + 1 (0 = none)
-                       // (a batched propagator keeps its span_blocks in `rows`)
+                       // (a batched propagator keeps its span_blocks in `rows`);
+                       // 1D/2D stencils: 1 = the library's own choice was faster
+                       // than every geometry that can be named
 };
 
 TuneKey tune_key_1d(int dtype, int64_t n, int steps, bool ghost);
@@ -32,6 +34,7 @@ TuneKey tune_key_batched(int dtype, int64_t total_cells, int count, int steps);
 
 bool tune_lookup(const TuneKey& k, TunedGeom* g);
 void tune_store(const TuneKey& k, const TunedGeom& g);
+void tune_erase(const TuneKey& k);
 
 // Default 1D geometry for a key: the tuned entry if one exists, otherwise the
 // built-in heuristic.
