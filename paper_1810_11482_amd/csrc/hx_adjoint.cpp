@@ -132,14 +132,12 @@ hx_status hx_heat_vc_forward(hx_ctx ctx, const hx_vc_args* a, const hx_event* de
         if (t % S == 0) return pck + (size_t)(t / S - 1) * bytes;
         return pw + (size_t)(t % 2) * bytes;
     };
-    // Aligned grids run each stretch between kept states (u0, the checkpoints,
-    // uT) in fused passes of up to kVcFusedMax steps, as even as the stretch
-    // allows, ping-ponging through the two work states; the others step by
-    // step.  Both give the same bits.
+    // Grids the fused kernels take run each stretch between kept states (u0,
+    // the checkpoints, uT) in fused passes of up to kVcFusedMax steps, as even
+    // as the stretch allows, ping-ponging through the two work states; the
+    // others step by step.  Both give the same bits.
     VCArgs probe{pu0, pk, nullptr, puT, nullptr, nx, ny, tau, rows};
-    const bool fused = vc_fused_supported(dt, probe) &&
-                       (T <= 1 || (((uintptr_t)pw & 15u) == 0 && (bytes & 15u) == 0)) &&
-                       (sc.nseg <= 1 || (((uintptr_t)pck & 15u) == 0));
+    const bool fused = vc_fused_supported(dt, probe);
     return c->submit(SC_COMPUTE, deps, ndeps, acc, "heat_vc_forward",
                      [=](hipStream_t st) -> hipError_t {
                          if (T == 0)
@@ -204,18 +202,14 @@ hx_status hx_heat_vc_backward(hx_ctx ctx, const hx_vc_args* a, const hx_event* d
         return (t + 1 == T) ? plT : pw + (size_t)((t + 1) % 2) * bytes;
     };
     auto lam_out = [=](int t) -> char* { return t == 0 ? pl0 : pw + (size_t)(t % 2) * bytes; };
-    // Aligned grids recompute each segment's states in fused passes that store
-    // every level (one read of the state and of kappa per pass instead of per
-    // step); the others step by step.  Both give the same bits.
+    // Grids the fused kernels take recompute each segment's states in fused
+    // passes that store every level (one read of the state and of kappa per
+    // pass instead of per step), and run the reverse sweep in fused passes of
+    // up to four adjoint steps with their gradient terms (lam moving between
+    // the two work slots, the last pass into lam0); the others step by step.
+    // Both give the same bits.
     VCArgs probe{pu0, pk, nullptr, pseg ? pseg : pu0, nullptr, nx, ny, tau, rows};
-    const bool fused = vc_fused_supported(dt, probe) && (bytes & 15u) == 0 &&
-                       (!pseg || ((uintptr_t)pseg & 15u) == 0) &&
-                       (sc.nseg <= 1 || ((uintptr_t)pck & 15u) == 0);
-    // ... and run the reverse sweep in fused passes of up to four adjoint
-    // steps with their gradient terms (lam moving between the two work slots,
-    // the last pass into lam0)
-    auto al16 = [](const void* q) { return ((uintptr_t)q & 15u) == 0; };
-    const bool fused_adj = fused && al16(plT) && al16(pl0) && al16(pga) && (T <= 1 || al16(pw));
+    const bool fused = vc_fused_supported(dt, probe);
     return c->submit(
         SC_COMPUTE, deps, ndeps, acc, "heat_vc_backward",
         [=](hipStream_t st) -> hipError_t {
@@ -253,7 +247,7 @@ hx_status hx_heat_vc_backward(hx_ctx ctx, const hx_vc_args* a, const hx_event* d
                         if ((e = launch_vc_step(dt, false, v, st)) != hipSuccess) return e;
                     }
                 }
-                if (fused_adj) {  // reverse sweep, fused
+                if (fused) {  // reverse sweep, fused
                     // at most two steps per FP64 pass: deeper FP64 passes need
                     // more than the 512 registers a wave can hold and spill
                     // hundreds of them to scratch (any depth gives the same bits)

@@ -381,12 +381,11 @@ struct VCArgs {
 
 hipError_t launch_vc_step(int dtype, bool adjoint, const VCArgs& v, hipStream_t stream);
 // `steps` (1..4) forward steps fused in one pass, u -> out (the same bits as
-// that many single steps); for grids whose rows are 16-byte aligned with nx a
-// multiple of 4 and under 2 GiB (vc_fused_supported), else hipErrorInvalidValue.
+// that many single steps); for grids with nx >= 4 and under 2 GiB
+// (vc_fused_supported), else hipErrorInvalidValue.
 constexpr int kVcFusedMax = 4;
 bool vc_fused_supported(int dtype, const VCArgs& v);
-// mid (16-byte aligned, stride a multiple of 16 of at least one state):
-// also store the states after steps 1 .. steps-1 at mid + (k-1) * mid_stride.
+// mid (stride of at least one state): also store the states after steps 1 .. steps-1 at mid + (k-1) * mid_stride.
 hipError_t launch_vc_forward(int dtype, int steps, const VCArgs& v, hipStream_t stream,
                              void* mid = nullptr, int64_t mid_stride = 0);
 // `steps` (1..4) adjoint steps t = tb .. tb-steps+1 fused in one pass: v.lam
@@ -395,8 +394,8 @@ hipError_t launch_vc_forward(int dtype, int steps, const VCArgs& v, hipStream_t 
 // bits as that many launch_vc_step adjoint steps); ustates[k] is u_t of step
 // t = tb - k.  zero_in: the accumulator starts at zero (not read);
 // fold_total: add the accumulator to this FP64 total (the segment's fold)
-// instead of storing it.  The grids vc_fused_supported takes, lam, gacc, the
-// total and the states 16-byte aligned, else hipErrorInvalidValue.
+// instead of storing it.  The grids vc_fused_supported takes, else
+// hipErrorInvalidValue.
 hipError_t launch_vc_adjoint(int dtype, int steps, const VCArgs& v, const void* const* ustates,
                              hipStream_t stream, bool zero_in = false,
                              double* fold_total = nullptr);

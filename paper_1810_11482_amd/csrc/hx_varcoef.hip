@@ -455,6 +455,109 @@ __device__ __forceinline__ uint32_t xcd_block(uint32_t b, uint32_t n) {
     return x * q + (x < r ? x : r) + b / X;
 }
 
+// A lane's cells in the fused passes.  Lanes hold C adjacent columns; on a
+// grid whose rows are a multiple of C cells a lane's cells are all inside or
+// all outside the domain.  RAG (any other row length): one lane per row
+// straddles its end, and its cells past nx are kept at the ghost value 0.
+// Rows need no alignment: vectors are loaded and stored with the alignment of
+// one element.
+template <typename T, bool RAG>
+struct Lane {
+    int64_t xl;       // first column
+    bool lin;         // some of the lane's cells lie inside the domain
+    bool wok, eok;    // cell 0's west face, cell C-1's east face is interior
+    bool part;        // RAG: the lane's cells straddle the row's end
+    bool in[C];       // RAG: the cell lies inside
+    bool ei[C];       // RAG: the cell's east face is interior
+    bool any_part;    // RAG, wave-uniform: some lane of the wave straddles
+};
+
+template <typename T, bool RAG>
+__device__ __forceinline__ Lane<T, RAG> make_lane(int64_t xl, int64_t nx) {
+    Lane<T, RAG> l;
+    l.xl = xl;
+    l.lin = xl >= 0 && (RAG ? xl < nx : xl + C <= nx);
+    l.wok = xl >= 1;
+    l.eok = xl + C < nx;
+    l.part = RAG && l.lin && xl + C > nx;
+    l.any_part = RAG && __ballot(l.part) != 0;
+#pragma unroll
+    for (int j = 0; j < C; ++j) {
+        l.in[j] = xl + j >= 0 && xl + j < nx;
+        l.ei[j] = xl + j + 1 < nx;
+    }
+    return l;
+}
+
+template <typename T> struct VecU;
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef double f64x2u __attribute__((ext_vector_type(2), aligned(8)));
+template <> struct VecU<float> { typedef f32x4u t; };
+template <> struct VecU<double> { typedef f64x2u t; };
+
+// Row y (clamped into the grid) of f at the lane's columns; lanes outside the
+// domain read column 0 (never used).  RAG: the straddling lane's vector runs on
+// into the next row (cells past nx are never used); in the last row, where
+// that would leave the array, it is read C - (nx mod C) cells earlier and
+// shifted back.  No load sits under a branch.
+template <typename T, bool RAG, bool NT>
+__device__ __forceinline__ void load_lane(const T* f, const Lane<T, RAG>& l, int64_t y, int64_t nx,
+                                          int64_t ny, T (&v)[C]) {
+    typedef typename VecU<T>::t UT;
+    typedef __attribute__((address_space(1))) const UT GU;
+    constexpr int VN = 16 / sizeof(T);
+    const int64_t yc = y < 0 ? 0 : (y >= ny ? ny - 1 : y);
+    const bool last = RAG && l.any_part && yc == ny - 1;
+    const int64_t x = !l.lin ? 0 : (last && l.part ? nx - C : l.xl);
+    const T* p = f + yc * nx + x;
+#pragma unroll
+    for (int q = 0; q < C / VN; ++q) {
+        const UT r = NT ? __builtin_nontemporal_load((GU*)(p + q * VN)) : *(GU*)(p + q * VN);
+#pragma unroll
+        for (int e = 0; e < VN; ++e) v[q * VN + e] = r[e];
+    }
+    if constexpr (RAG)
+        if (last) {
+            const int k = l.part ? C - (int)(nx - l.xl) : 0;  // cells to shift by
+#pragma unroll
+            for (int j = 0; j < C; ++j) {
+                T x1 = v[j + 1 < C ? j + 1 : C - 1], x2 = v[j + 2 < C ? j + 2 : C - 1];
+                const T x3 = v[C - 1];
+                v[j] = k == 0 ? v[j] : (k == 1 ? x1 : (k == 2 ? x2 : x3));
+            }
+        }
+}
+
+// One cell of a straddling lane's store (an out-of-range offset drops it).
+__device__ __forceinline__ void store_cell(__amdgpu_buffer_rsrc_t rs, float v, uint32_t off) {
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), rs, (int)off, 0, 0);
+}
+__device__ __forceinline__ void store_cell(__amdgpu_buffer_rsrc_t rs, double v, uint32_t off) {
+    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+    u32x2 bits;
+    __builtin_memcpy(&bits, &v, sizeof(bits));
+    __builtin_amdgcn_raw_buffer_store_b64(bits, rs, (int)off, 0, 0);
+}
+
+// store_row_if for the fused passes: `off` is the offset of a lane whose cells
+// are all stored (else out of range); a straddling lane stores its inside
+// cells one by one, in the waves that have one.
+template <typename T, bool RAG, int AUX = 0>
+__device__ __forceinline__ void store_lane_if(__amdgpu_buffer_rsrc_t rs, const Lane<T, RAG>& l,
+                                              uint32_t off, bool ok, int64_t y, int64_t nx,
+                                              const T (&v)[C]) {
+    store_row_if<T, AUX>(rs, off, ok, y, nx, v);
+    if constexpr (RAG)
+        if (l.any_part) {
+#pragma unroll
+            for (int j = 0; j < C; ++j)
+                store_cell(rs, v[j],
+                           ok && l.part && l.in[j]
+                               ? (uint32_t)((y * nx + l.xl + j) * (int64_t)sizeof(T))
+                               : OOB_OFFSET);
+        }
+}
+
 // Face conductivities of one row for a lane's C cells, as the single step
 // forms them: the east face of cell j, (kappa_j + kappa_{j+1}) / 2, in e[j]
 // (kappa_{j+1} = kappa_j on the domain's east edge) and cell 0's west face in
@@ -463,22 +566,22 @@ __device__ __forceinline__ uint32_t xcd_block(uint32_t b, uint32_t n) {
 // (kappa_{rho-1} + kappa_rho) / 2, in s: the north face of row rho is the
 // south face of row rho - 1.  Rows outside the domain are clamped reads of the
 // edge row, so the edge faces come out as (kappa + kappa) / 2 = kappa.
-template <typename T>
-__device__ __forceinline__ void row_faces(const T (&kc)[C], const T (&ka)[C], bool wok, bool eok,
-                                          T (&e)[C + 1], T (&s)[C]) {
+template <typename T, bool RAG>
+__device__ __forceinline__ void row_faces(const T (&kc)[C], const T (&ka)[C],
+                                          const Lane<T, RAG>& l, T (&e)[C + 1], T (&s)[C]) {
     const T kel = dpp_move<DPP_WAVE_SHL1>(kc[0]);
     const T kwl = dpp_move<DPP_WAVE_SHR1>(kc[C - 1]);
 #pragma unroll
-    for (int j = 0; j + 1 < C; ++j) e[j] = (kc[j] + kc[j + 1]) * T(0.5);
-    e[C - 1] = (kc[C - 1] + (eok ? kel : kc[C - 1])) * T(0.5);
-    e[C] = (kc[0] + (wok ? kwl : kc[0])) * T(0.5);
+    for (int j = 0; j + 1 < C; ++j)
+        e[j] = (kc[j] + (!RAG || l.ei[j] ? kc[j + 1] : kc[j])) * T(0.5);
+    e[C - 1] = (kc[C - 1] + (l.eok ? kel : kc[C - 1])) * T(0.5);
+    e[C] = (kc[0] + (l.wok ? kwl : kc[0])) * T(0.5);
 #pragma unroll
     for (int j = 0; j < C; ++j) s[j] = (ka[j] + kc[j]) * T(0.5);
 }
 
-// D fused forward steps (temporal blocking), for aligned grids (every row
-// 16-byte aligned, nx a multiple of C, under 2 GiB).  A wave owns 64*C
-// columns, of which lanes 1..62 are its output: the strips overlap by one
+// D fused forward steps (temporal blocking), for grids under 2 GiB with nx >= C
+// (RAG: nx not a multiple of C).  A wave owns 64*C columns, of which lanes 1..62 are its output: the strips overlap by one
 // lane on each side, and the outer lanes' values go stale one column per step
 // (from lanes 0 and 63 inward), which D <= C steps keep out of lanes 1..62.
 // Rows stream top to bottom once: input row i (u and kappa) enters level 0;
@@ -495,13 +598,10 @@ __device__ __forceinline__ void row_faces(const T (&kc)[C], const T (&ka)[C], bo
 // * mid_stride bytes (the states between the pass's input and its output, as
 // the checkpointed backward sweep recomputes them): one read of u and kappa and
 // D writes for D steps.
-template <typename T, int D, bool MID>
+template <typename T, int D, bool MID, bool RAG>
 __global__ __launch_bounds__(256) void k_vc_fwd(VCDev a, int64_t nstrips, int64_t nwaves,
                                                 void* mid, int64_t mid_stride) {
     static_assert(D >= 1 && D <= C && D <= 5, "the halo lane covers at most C steps");
-    typedef T V2 __attribute__((ext_vector_type(16 / sizeof(T))));
-    typedef __attribute__((address_space(1))) const V2 GV2;
-    constexpr int VN = 16 / sizeof(T);
     constexpr int W = S - 2 * C;  // output columns per strip
     const int wpg = blockDim.x >> 6;
     const int64_t wave = (int64_t)xcd_block(blockIdx.x, gridDim.x) * wpg +
@@ -516,30 +616,20 @@ __global__ __launch_bounds__(256) void k_vc_fwd(VCDev a, int64_t nstrips, int64_
     const T dt = static_cast<T>(a.dt);
     const T* U = static_cast<const T*>(a.u);
     const T* K = static_cast<const T*>(a.kappa);
-    const bool lin = xl >= 0 && xl + C <= nx;  // the lane's cells: all inside or all outside
-    const int64_t xv = lin ? xl : 0;
-    const bool wok = xl >= 1;       // cell 0's west face is interior
-    const bool eok = xl + C < nx;   // cell C-1's east face is interior
-    // row y of f for this lane, from a clamped row address (values of lanes
-    // outside the domain are never used).  A pass reads each row once (a
-    // chunk's halo rows twice); nontemporal loads measured faster where the
-    // pass stores one row per row read (5.3 against 4.4 TB/s), cached loads
-    // where it stores every level (MID)
+    const Lane<T, RAG> ln = make_lane<T, RAG>(xl, nx);
+    // row y of f for this lane.  A pass reads each row once (a chunk's halo
+    // rows twice); nontemporal loads measured faster where the pass stores one
+    // row per row read (5.3 against 4.4 TB/s), cached loads where it stores
+    // every level (MID)
     auto raw = [&](const T* f, int64_t y, T (&v)[C]) {
-        const T* row = f + (y < 0 ? 0 : (y >= ny ? ny - 1 : y)) * nx;
-#pragma unroll
-        for (int q = 0; q < C / VN; ++q) {
-            const V2 x = MID ? *((GV2*)(row + xv) + q)
-                             : __builtin_nontemporal_load((GV2*)(row + xv) + q);
-#pragma unroll
-            for (int e = 0; e < VN; ++e) v[q * VN + e] = x[e];
-        }
+        load_lane<T, RAG, !MID>(f, ln, y, nx, ny, v);
     };
     const int bytes = (int)(ny * nx * (int64_t)sizeof(T));
     const __amdgpu_buffer_rsrc_t rso =
         __builtin_amdgcn_make_buffer_rsrc(a.out, (short)0, bytes, BUF_DWORD3);
-    const bool store_lane = lane >= 1 && lane <= 62 && lin;
-    const uint32_t lane_off = store_lane ? (uint32_t)(xl * (int64_t)sizeof(T)) : OOB_OFFSET;
+    const bool store_lane = lane >= 1 && lane <= 62 && ln.lin;
+    const uint32_t lane_off =
+        store_lane && !ln.part ? (uint32_t)(xl * (int64_t)sizeof(T)) : OOB_OFFSET;
     __amdgpu_buffer_rsrc_t rsm[D > 1 ? D - 1 : 1];
     if constexpr (MID)
 #pragma unroll
@@ -580,13 +670,13 @@ __global__ __launch_bounds__(256) void k_vc_fwd(VCDev a, int64_t nstrips, int64_
         const bool iin = i >= 0 && i < ny;
 #pragma unroll
         for (int j = 0; j < C; ++j) {
-            fr[0][m3(P)][j] = iin ? upf[Q][j] : T(0);
+            fr[0][m3(P)][j] = iin && (!RAG || ln.in[j]) ? upf[Q][j] : T(0);
             kr[m3(P)][j] = kpf[Q][j];
         }
         // row i+PF in flight (rows past the domain are clamped reads)
         raw(U, i + PF, upf[Q]);
         raw(K, i + PF, kpf[Q]);
-        row_faces<T>(kr[m3(P)], kr[m3(P - 1)], wok, eok, ef[m6(P)], sf[m6(P - 1)]);
+        row_faces<T, RAG>(kr[m3(P)], kr[m3(P - 1)], ln, ef[m6(P)], sf[m6(P - 1)]);
         T out[C];
 #pragma unroll
         for (int k = 1; k <= D; ++k) {
@@ -603,8 +693,8 @@ __global__ __launch_bounds__(256) void k_vc_fwd(VCDev a, int64_t nstrips, int64_
 #pragma unroll
             for (int j = 0; j < C; ++j) {
                 const T fc = f0[j];
-                const T fW = j > 0 ? f0[j - 1] : (wok ? fwl : T(0));
-                const T fE = j + 1 < C ? f0[j + 1] : (eok ? fel : T(0));
+                const T fW = j > 0 ? f0[j - 1] : (ln.wok ? fwl : T(0));
+                const T fE = j + 1 < C ? f0[j + 1] : (ln.eok ? fel : T(0));
                 const T kfw = j > 0 ? e[j - 1] : e[C];
                 T acc = kfw * (fW - fc);
                 acc = fmaT(e[j], fE - fc, acc);
@@ -615,16 +705,17 @@ __global__ __launch_bounds__(256) void k_vc_fwd(VCDev a, int64_t nstrips, int64_
             if (k < D) {
                 const bool rin = r >= 0 && r < ny;
 #pragma unroll
-                for (int j = 0; j < C; ++j) fr[k][m3(P - k)][j] = rin ? v[j] : T(0);
+                for (int j = 0; j < C; ++j)
+                    fr[k][m3(P - k)][j] = rin && (!RAG || ln.in[j]) ? v[j] : T(0);
                 if constexpr (MID)
-                    store_row_if<T>(rsm[k - 1], lane_off, r >= y0 && r < y1, r, nx, v);
+                    store_lane_if<T, RAG>(rsm[k - 1], ln, lane_off, r >= y0 && r < y1, r, nx, v);
             } else {
 #pragma unroll
                 for (int j = 0; j < C; ++j) out[j] = v[j];
             }
         }
         const int64_t r = i - D;
-        store_row_if<T>(rso, lane_off, r >= y0 && r < y1, r, nx, out);
+        store_lane_if<T, RAG>(rso, ln, lane_off, r >= y0 && r < y1, r, nx, out);
     };
     // whole groups of six rows (one exit keeps the rings in registers): the
     // up to five rows past the pass's last are clamped reads and not stored
@@ -660,13 +751,10 @@ struct UStates {
     const void* p[4];
 };
 
-template <typename T, int D, bool ZIN, bool FOLD>
+template <typename T, int D, bool ZIN, bool FOLD, bool RAG>
 __global__ __launch_bounds__(256) void k_vc_adj(VCDev a, UStates us, double* __restrict__ total,
                                                 int64_t nstrips, int64_t nwaves) {
     static_assert(D >= 1 && D <= C && D <= 4, "the halo lane covers at most C steps");
-    typedef T V2 __attribute__((ext_vector_type(16 / sizeof(T))));
-    typedef __attribute__((address_space(1))) const V2 GV2;
-    constexpr int VN = 16 / sizeof(T);
     constexpr int W = S - 2 * C;  // output columns per strip
     const int wpg = blockDim.x >> 6;
     const int64_t wave = (int64_t)xcd_block(blockIdx.x, gridDim.x) * wpg +
@@ -682,26 +770,18 @@ __global__ __launch_bounds__(256) void k_vc_adj(VCDev a, UStates us, double* __r
     const T* L = static_cast<const T*>(a.lam);
     const T* K = static_cast<const T*>(a.kappa);
     const T* G = static_cast<const T*>(a.gacc);
-    const bool lin = xl >= 0 && xl + C <= nx;  // the lane's cells: all inside or all outside
-    const int64_t xv = lin ? xl : 0;
-    const bool wok = xl >= 1;       // cell 0's west face is interior
-    const bool eok = xl + C < nx;   // cell C-1's east face is interior
+    const Lane<T, RAG> ln = make_lane<T, RAG>(xl, nx);
     auto raw = [&](const T* f, int64_t y, T (&v)[C]) {
-        const T* row = f + (y < 0 ? 0 : (y >= ny ? ny - 1 : y)) * nx;
-#pragma unroll
-        for (int q = 0; q < C / VN; ++q) {
-            const V2 x = *((GV2*)(row + xv) + q);
-#pragma unroll
-            for (int e = 0; e < VN; ++e) v[q * VN + e] = x[e];
-        }
+        load_lane<T, RAG, false>(f, ln, y, nx, ny, v);
     };
     const int bytes = (int)(ny * nx * (int64_t)sizeof(T));
     const __amdgpu_buffer_rsrc_t rso =
         __builtin_amdgcn_make_buffer_rsrc(a.out, (short)0, bytes, BUF_DWORD3);
     const __amdgpu_buffer_rsrc_t rsg =
         __builtin_amdgcn_make_buffer_rsrc(a.gacc, (short)0, bytes, BUF_DWORD3);
-    const bool store_lane = lane >= 1 && lane <= 62 && lin;
-    const uint32_t lane_off = store_lane ? (uint32_t)(xl * (int64_t)sizeof(T)) : OOB_OFFSET;
+    const bool store_lane = lane >= 1 && lane <= 62 && ln.lin;
+    const uint32_t lane_off =
+        store_lane && !ln.part ? (uint32_t)(xl * (int64_t)sizeof(T)) : OOB_OFFSET;
 
     T lr[D][3][C];    // lam of level k (level 0: lam_{tb+1})
     T ur[D][3][C];    // u_t read by level k + 1
@@ -742,7 +822,7 @@ __global__ __launch_bounds__(256) void k_vc_adj(VCDev a, UStates us, double* __r
         const bool iin = i >= 0 && i < ny;
 #pragma unroll
         for (int j = 0; j < C; ++j) {
-            lr[0][m3(P)][j] = iin ? lpf[Q][j] : T(0);
+            lr[0][m3(P)][j] = iin && (!RAG || ln.in[j]) ? lpf[Q][j] : T(0);
             kr[m3(P)][j] = kpf[Q][j];
             gr[m6(P - 1)][j] = ZIN ? T(0) : gpf[Q][j];
         }
@@ -756,7 +836,7 @@ __global__ __launch_bounds__(256) void k_vc_adj(VCDev a, UStates us, double* __r
         if (!ZIN) raw(G, i + PF - 1, gpf[Q]);
 #pragma unroll
         for (int k = 0; k < D; ++k) raw(static_cast<const T*>(us.p[k]), i + PF - k, upf[Q][k]);
-        row_faces<T>(kr[m3(P)], kr[m3(P - 1)], wok, eok, ef[m6(P)], sf[m6(P - 1)]);
+        row_faces<T, RAG>(kr[m3(P)], kr[m3(P - 1)], ln, ef[m6(P)], sf[m6(P - 1)]);
         T out[C];
 #pragma unroll
         for (int k = 1; k <= D; ++k) {
@@ -781,9 +861,10 @@ __global__ __launch_bounds__(256) void k_vc_adj(VCDev a, UStates us, double* __r
             for (int j = 0; j < C; ++j) {
                 const T fc = f0[j];
                 const T uc = u0[j];
-                const bool wi = j > 0 || wok, ei = j + 1 < C || eok;
-                const T fW = j > 0 ? f0[j - 1] : (wok ? fwl : T(0));
-                const T fE = j + 1 < C ? f0[j + 1] : (eok ? fel : T(0));
+                const bool wi = j > 0 || ln.wok;
+                const bool ei = j + 1 < C ? (!RAG || ln.ei[j]) : ln.eok;
+                const T fW = j > 0 ? f0[j - 1] : (ln.wok ? fwl : T(0));
+                const T fE = j + 1 < C ? f0[j + 1] : (ln.eok ? fel : T(0));
                 const T uw = j > 0 ? u0[j - 1] : uwl;
                 const T ue = j + 1 < C ? u0[j + 1] : uel;
                 const T kfw = j > 0 ? e[j - 1] : e[C];
@@ -805,7 +886,8 @@ __global__ __launch_bounds__(256) void k_vc_adj(VCDev a, UStates us, double* __r
             if (k < D) {
                 const bool rin = r >= 0 && r < ny;
 #pragma unroll
-                for (int j = 0; j < C; ++j) lr[k][m3(P - k)][j] = rin ? v[j] : T(0);
+                for (int j = 0; j < C; ++j)
+                    lr[k][m3(P - k)][j] = rin && (!RAG || ln.in[j]) ? v[j] : T(0);
             } else {
 #pragma unroll
                 for (int j = 0; j < C; ++j) out[j] = v[j];
@@ -813,15 +895,16 @@ __global__ __launch_bounds__(256) void k_vc_adj(VCDev a, UStates us, double* __r
         }
         const int64_t r = i - D;
         const bool rout = r >= y0 && r < y1;
-        store_row_if<T, ST_NT>(rso, lane_off, rout, r, nx, out);
+        store_lane_if<T, RAG, ST_NT>(rso, ln, lane_off, rout, r, nx, out);
         if constexpr (FOLD) {
             if (rout && store_lane) {
                 double* tp = total + r * nx + xl;
 #pragma unroll
-                for (int j = 0; j < C; ++j) tp[j] += (double)gr[m6(P - D)][j];
+                for (int j = 0; j < C; ++j)
+                    if (!RAG || ln.in[j]) tp[j] += (double)gr[m6(P - D)][j];
             }
         } else {
-            store_row_if<T, ST_NT>(rsg, lane_off, rout, r, nx, gr[m6(P - D)]);
+            store_lane_if<T, RAG, ST_NT>(rsg, ln, lane_off, rout, r, nx, gr[m6(P - D)]);
         }
     };
     // whole groups of six rows (one exit keeps the rings in registers): the
@@ -867,40 +950,51 @@ hipError_t launch_vc_step(int dtype, bool adjoint, const VCArgs& v, hipStream_t 
 }
 
 bool vc_fused_supported(int dtype, const VCArgs& v) {
-    auto al = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; };
     const int es = dtype == 0 ? 4 : 8;
-    return v.nx % C == 0 && (v.nx * es) % 16 == 0 && al(v.u) && al(v.kappa) && al(v.out) &&
-           v.nx * v.ny * es < (int64_t(1) << 31) && v.nx > 0 && v.ny > 0;
+    return v.nx >= C && v.ny > 0 && v.nx * v.ny * es < (int64_t(1) << 31);
 }
 
 // The fused kernel for (dtype, steps, variant): variant bit 0 = MID (forward)
 // or ZIN (adjoint), bit 1 = FOLD (adjoint).
-template <typename T>
+template <typename T, bool RAG>
 const void* fused_kernel(bool adjoint, int steps, int variant) {
-#define HX_VC_FWD_K(D) (variant & 1) ? (const void*)k_vc_fwd<T, D, true> : (const void*)k_vc_fwd<T, D, false>
+#define HX_VC_FWD_K(D)                                                                  \
+    (variant & 1) ? (const void*)k_vc_fwd<T, D, true, RAG> : (const void*)k_vc_fwd<T, D, false, RAG>
 #define HX_VC_ADJ_K(D)                                                                   \
-    variant == 3   ? (const void*)k_vc_adj<T, D, true, true>                             \
-    : variant == 1 ? (const void*)k_vc_adj<T, D, true, false>                            \
-    : variant == 2 ? (const void*)k_vc_adj<T, D, false, true>                            \
-                   : (const void*)k_vc_adj<T, D, false, false>
+    variant == 3   ? (const void*)k_vc_adj<T, D, true, true, RAG>                        \
+    : variant == 1 ? (const void*)k_vc_adj<T, D, true, false, RAG>                       \
+    : variant == 2 ? (const void*)k_vc_adj<T, D, false, true, RAG>                       \
+                   : (const void*)k_vc_adj<T, D, false, false, RAG>
     switch (steps) {
         case 1: return adjoint ? (HX_VC_ADJ_K(1)) : (HX_VC_FWD_K(1));
         case 2: return adjoint ? (HX_VC_ADJ_K(2)) : (HX_VC_FWD_K(2));
-        case 3: return adjoint ? (HX_VC_ADJ_K(3)) : (HX_VC_FWD_K(3));
-        case 4: return adjoint ? (HX_VC_ADJ_K(4)) : (HX_VC_FWD_K(4));
-        default: return nullptr;
+        default: break;
     }
+    // the FP64 reverse sweep takes at most two steps per pass (deeper passes
+    // need more than a wave's 512 registers)
+    if constexpr (sizeof(T) == 4)
+        if (adjoint) return steps == 3 ? (HX_VC_ADJ_K(3)) : (steps == 4 ? (HX_VC_ADJ_K(4)) : nullptr);
+    if (adjoint) return nullptr;
+    return steps == 3 ? (HX_VC_FWD_K(3)) : (steps == 4 ? (HX_VC_FWD_K(4)) : nullptr);
 #undef HX_VC_FWD_K
 #undef HX_VC_ADJ_K
+}
+
+const void* fused_kernel(int dtype, int64_t nx, bool adjoint, int steps, int variant) {
+    if (nx % C)
+        return dtype == 0 ? fused_kernel<float, true>(adjoint, steps, variant)
+                          : fused_kernel<double, true>(adjoint, steps, variant);
+    return dtype == 0 ? fused_kernel<float, false>(adjoint, steps, variant)
+                      : fused_kernel<double, false>(adjoint, steps, variant);
 }
 
 // Rows per chunk when the caller leaves the choice to the library: enough
 // chunks that strips x chunks waves fill the device's resident wave slots for
 // this kernel once (one round of waves: no partly filled second round), at
-// least 16 rows.  A wave streams its chunk plus 2D halo rows, so taller
-// chunks also recompute fewer rows.  The result does not depend on the chunk
-// height.
-int fill_rows(const void* k, int64_t nstrips, int64_t ny) {
+// least 12 - 2D rows (two groups of the six-row loop).  A wave streams its
+// chunk plus 2D halo rows, so taller chunks also recompute fewer rows.  The
+// result does not depend on the chunk height.
+int fill_rows(const void* k, int64_t nstrips, int64_t ny, int depth) {
     static std::mutex mu;
     static std::vector<std::pair<std::pair<const void*, int>, int64_t>> cache;
     int dev = 0;
@@ -927,15 +1021,15 @@ int fill_rows(const void* k, int64_t nstrips, int64_t ny) {
         cache.push_back({{k, dev}, slots});
     }
     const int64_t chunks = std::max<int64_t>(1, slots / nstrips);
-    const int64_t rows = std::max<int64_t>(16, (ny + chunks - 1) / chunks);
+    const int64_t rows = std::max<int64_t>(12 - 2 * depth, (ny + chunks - 1) / chunks);
     return (int)std::min<int64_t>(rows, int64_t(1) << 30);
 }
 
-hipError_t launch_fused(const void* k, VCDev a, int rows_req, void* arg3, void* arg4,
+hipError_t launch_fused(const void* k, VCDev a, int depth, int rows_req, void* arg3, void* arg4,
                         bool adjoint, hipStream_t st) {
     if (!k) return hipErrorInvalidValue;
     int64_t nstrips = (a.nx + (S - 2 * C) - 1) / (S - 2 * C);
-    a.rows = rows_req > 0 ? rows_req : fill_rows(k, nstrips, a.ny);
+    a.rows = rows_req > 0 ? rows_req : fill_rows(k, nstrips, a.ny, depth);
     int64_t nwaves = nstrips * ((a.ny + a.rows - 1) / a.rows);
     const int wpg = 4;
     const int64_t groups = (nwaves + wpg - 1) / wpg;
@@ -950,32 +1044,26 @@ hipError_t launch_vc_forward(int dtype, int steps, const VCArgs& v, hipStream_t 
                              int64_t mid_stride) {
     if (steps < 1 || steps > C || !vc_fused_supported(dtype, v)) return hipErrorInvalidValue;
     const int es = dtype == 0 ? 4 : 8;
-    if (mid && (((reinterpret_cast<uintptr_t>(mid) | (uintptr_t)mid_stride) & 15u) ||
-                mid_stride < v.nx * v.ny * es))
-        return hipErrorInvalidValue;
+    if (mid && mid_stride < v.nx * v.ny * es) return hipErrorInvalidValue;
     VCDev a{v.u, v.kappa, nullptr, v.out, nullptr, v.nx, v.ny, v.dt, 0, 1};
     const int variant = mid ? 1 : 0;
-    const void* k = dtype == 0 ? fused_kernel<float>(false, steps, variant)
-                               : fused_kernel<double>(false, steps, variant);
-    return launch_fused(k, a, v.rows, &mid, &mid_stride, false, st);
+    const void* k = fused_kernel(dtype, v.nx, false, steps, variant);
+    return launch_fused(k, a, steps, v.rows, &mid, &mid_stride, false, st);
 }
 
 hipError_t launch_vc_adjoint(int dtype, int steps, const VCArgs& v, const void* const* ustates,
                              hipStream_t st, bool zero_in, double* fold_total) {
-    auto al = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; };
-    if (steps < 1 || steps > C || steps > 4 || !v.lam || !v.gacc || !al(v.lam) || !al(v.gacc) ||
-        !al(fold_total) || !vc_fused_supported(dtype, v))
+    if (steps < 1 || steps > C || steps > 4 || !v.lam || !v.gacc || !vc_fused_supported(dtype, v))
         return hipErrorInvalidValue;
     UStates us{};
     for (int k = 0; k < steps; ++k) {
-        if (!ustates[k] || !al(ustates[k])) return hipErrorInvalidValue;
+        if (!ustates[k]) return hipErrorInvalidValue;
         us.p[k] = ustates[k];
     }
     VCDev a{nullptr, v.kappa, v.lam, v.out, v.gacc, v.nx, v.ny, v.dt, 0, 1};
     const int variant = (zero_in ? 1 : 0) | (fold_total ? 2 : 0);
-    const void* k = dtype == 0 ? fused_kernel<float>(true, steps, variant)
-                               : fused_kernel<double>(true, steps, variant);
-    return launch_fused(k, a, v.rows, &us, &fold_total, true, st);
+    const void* k = fused_kernel(dtype, v.nx, true, steps, variant);
+    return launch_fused(k, a, steps, v.rows, &us, &fold_total, true, st);
 }
 
 hipError_t launch_fold(int dtype, void* acc, double* total, int64_t n, hipStream_t st) {
