@@ -78,6 +78,14 @@ inline int64_t tiles_1d(const Seg1D& s, const Geom1D& g) {
     return (s.n + s.shift + w - 1) / w;
 }
 
+// The tile geometry of a pass of `depth` steps over `count` runs of n[i] cells
+// when the caller leaves it to the library (hx_stencil1d.hip says where the
+// lines lie); *us receives the pass's modelled time.  depth must fit 16 cells
+// per lane.
+Geom1D choose_geom1d(int dtype, const int64_t* n, int count, int depth, double* us);
+// Pass depths of a run of `steps` steps over n cells, in the library's choice.
+std::vector<int> choose_depths1d(int dtype, int64_t n, int steps);
+
 // dtype: 0 = f32, 1 = f64.  Returns hipSuccess or the launch error.
 hipError_t launch_stencil1d(int dtype, const Seg1D& seg, const Geom1D& g, hipStream_t stream);
 

@@ -23,6 +23,9 @@
 // count, not on the tile geometry.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <cmath>
+
 #include "hx_internal.h"
 
 namespace hx {
@@ -571,6 +574,76 @@ hipError_t launch_batched(const Seg1D* segs, const uint32_t* tseg, const uint32_
 #undef HX_CPL_SWITCH4
 
 }  // namespace
+
+namespace {
+
+// Modelled time of one pass, us: a + max(D l, D w i + w m) with w the waves per
+// SIMD (counted up to whole ones while they are few), l a lone wave's step, i a
+// step's share of a full SIMD and m a tile's loads and stores.  Fitted to
+// passes of 5 to 200 steps over 12 lines from 1000 to 2^26 cells (mean
+// deviation 7-14 %).  Few cells per lane keep the serial chain of a step short
+// (8 cells 0.07 us, 32 cells 0.17) and give short lines more waves; many keep
+// the recomputed halo small, which is what counts once the SIMDs are full.
+// Measured, 200 float steps: 20000 cells 19 us in one pass of 8 cells per lane
+// against 101 us in four of 32; 2^20 cells 28 against 100 (one pass, 16);
+// 12345679 cells 134 against 180 (one pass, 32).
+struct LineCost {
+    int cpl;
+    double a, l, i, m;
+};
+constexpr LineCost kLineCost[2][4] = {
+    {{8, 4.88, 0.071, 0.0223, 0.351}, {16, 7.78, 0.103, 0.0446, 0.662},
+     {32, 11.1, 0.170, 0.0692, 2.01}, {64, 22.5, 0.301, 0.159, 3.90}},
+    {{8, 4.77, 0.082, 0.0322, 0.878}, {16, 8.59, 0.098, 0.0614, 1.56},
+     {32, 11.7, 0.166, 0.123, 4.15}, {64, 22.3, 0.317, 0.294, 12.2}}};
+constexpr int kLineDepth = 200;  // deepest pass considered (the deepest measured)
+
+}  // namespace
+
+Geom1D choose_geom1d(int dtype, const int64_t* n, int count, int depth, double* us) {
+    const int vn = dtype ? 2 : 4;
+    Geom1D g{};
+    g.steps = depth;
+    g.halo = depth > vn ? (depth + vn - 1) / vn * vn : vn;
+    g.wpg = 4;
+    *us = 0.0;
+    for (const LineCost& c : kLineCost[dtype ? 1 : 0]) {
+        const int64_t wout = 64LL * c.cpl - 2LL * g.halo;
+        if (wout < vn) continue;
+        int64_t waves = 0;
+        for (int k = 0; k < count; ++k) waves += (n[k] + wout - 1) / wout;
+        double w = (double)waves / 1024.0;
+        if (w > 1.0 && w < 6.0) w = 0.5 * (w + std::ceil(w - 0.05));
+        const double t = c.a + std::max(depth * c.l, depth * w * c.i + w * c.m);
+        if (*us == 0.0 || t < *us) {
+            *us = t;
+            g.cpl = c.cpl;
+        }
+    }
+    return g;
+}
+
+std::vector<int> choose_depths1d(int dtype, int64_t n, int steps) {
+    // np passes as even as they can be, np by the least modelled time
+    int best = 0;
+    double best_us = 0.0;
+    for (int np = (steps + kLineDepth - 1) / kLineDepth; np <= (steps + 4) / 5; ++np) {
+        const int d = steps / np, more = steps % np;
+        double us = 0.0, us1 = 0.0;
+        choose_geom1d(dtype, &n, 1, d, &us);
+        if (more) choose_geom1d(dtype, &n, 1, d + 1, &us1);
+        const double t = (np - more) * us + more * us1;
+        if (best == 0 || t < best_us) {
+            best = np;
+            best_us = t;
+        } else if (t > 2.0 * best_us) {
+            break;  // shallower passes only add launches from here
+        }
+    }
+    std::vector<int> plan;
+    for (int p = 0; p < best; ++p) plan.push_back(steps / best + (p < steps % best ? 1 : 0));
+    return plan;
+}
 
 hipError_t launch_stencil1d(int dtype, const Seg1D& seg, const Geom1D& g, hipStream_t stream) {
     return dtype == 0 ? launch_single<float>(seg, g, stream) : launch_single<double>(seg, g, stream);

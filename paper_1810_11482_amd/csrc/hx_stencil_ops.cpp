@@ -49,7 +49,11 @@ static hx_status launch_1d(Ctx* c, const hx_stencil_args* a, const hx_event* dep
 
     Geom1D g;
     TuneKey key = tune_key_1d(dt, n, a->steps, ghost);
-    Geom1D def = default_geom_1d(c, key);
+    Geom1D def{};
+    const bool tuned = tuned_geom_1d(key, &def);
+    // the library's own geometry of each pass, unless some of it is given or
+    // tuned
+    const bool choose = !tuned && !a->cells_per_lane && !a->waves_per_group;
     g.cpl = a->cells_per_lane ? a->cells_per_lane : def.cpl;
     if (g.cpl != 8 && g.cpl != 16 && g.cpl != 32 && g.cpl != 64)
         return c->fail(HX_ERR_ARG, "cells_per_lane must be 8, 16, 32 or 64");
@@ -83,8 +87,15 @@ static hx_status launch_1d(Ctx* c, const hx_stencil_args* a, const hx_event* dep
         return c->fail(HX_ERR_ARG, "time block " + std::to_string(D) + " exceeds the tile limit " +
                                        std::to_string(maxd) + " for cells_per_lane " +
                                        std::to_string(g.cpl));
-    const int passes = a->steps == 0 ? 1 : (a->steps + D - 1) / D;
-    if (passes > 1) {
+    std::vector<int> plan;  // fused depth of each pass
+    for (int left = a->steps; left > 0; left -= std::min(D, left)) plan.push_back(std::min(D, left));
+    if (plan.empty()) plan.push_back(0);
+    // (a run of more than one pass of time_block steps, or of 50, needs tmp
+    // whatever depths are chosen)
+    const bool need_tmp = plan.size() > 1;
+    if (choose && !a->time_block && need_tmp) plan = choose_depths1d(dt, n, a->steps);
+    const int passes = (int)plan.size();
+    if (need_tmp) {
         if (a->tmp == 0)
             return c->fail(HX_ERR_ARG, "a run of more than one pass needs a tmp buffer");
         s = resolve_range(c, a->tmp, a->tmp_offset, bytes, &ptmp, &ac, true);
@@ -103,28 +114,30 @@ static hx_status launch_1d(Ctx* c, const hx_stencil_args* a, const hx_event* dep
     seg.hw = a->halo_width;
     seg.halo_lo = plo;
     seg.halo_hi = phi;
-    const int steps = a->steps;
     const int vn = vec_cells(dt);
-    std::string what = "stencil1d n=" + std::to_string(n) + " steps=" + std::to_string(steps);
+    std::vector<Geom1D> geoms;
+    for (int d : plan) {
+        double us;
+        Geom1D gg = g;
+        gg.steps = d;
+        gg.halo = std::max(vn, round_up(d, vn));
+        geoms.push_back(choose && d <= max_time_block_1d(dt, 16) ? choose_geom1d(dt, &n, 1, d, &us)
+                                                                  : gg);
+    }
+    std::string what = "stencil1d n=" + std::to_string(n) + " steps=" + std::to_string(a->steps);
     return c->submit(
         SC_COMPUTE, deps, ndeps, acc, what,
         [=](hipStream_t st) -> hipError_t {
             // passes ping-pong so that the last one lands in out
             const char* src = pin;
-            int left = steps;
             for (int p = 0; p < passes; ++p) {
-                const int d = (p == passes - 1) ? left : D;
                 char* dst = ((passes - 1 - p) % 2 == 0) ? pout : ptmp;
                 Seg1D sg = seg;
                 sg.in = src;
                 sg.out = dst;
-                Geom1D gg = g;
-                gg.steps = d;
-                gg.halo = std::max(vn, round_up(d, vn));
-                hipError_t e = launch_stencil1d(dt, sg, gg, st);
+                hipError_t e = launch_stencil1d(dt, sg, geoms[p], st);
                 if (e != hipSuccess) return e;
                 src = dst;
-                left -= d;
             }
             return hipSuccess;
         },

@@ -98,24 +98,14 @@ void tune_erase(const TuneKey& k) {
     g_tune.erase(k.s);
 }
 
-Geom1D default_geom_1d(Ctx* c, const TuneKey& k) {
-    (void)c;
+bool tuned_geom_1d(const TuneKey& k, Geom1D* g) {
     TunedGeom t;
-    Geom1D g;
-    if (tune_lookup(k, &t) && t.cpl && t.mode == 0) {
-        g.cpl = t.cpl;
-        g.steps = t.steps;
-        g.wpg = t.wpg ? t.wpg : 4;
-        g.halo = 0;
-        return g;
-    }
-    // Heuristic: 32 cells per lane, a time block of up to 50 steps (the
-    // fastest measured on MI355X for long runs: 75% of the VALU issue rate).
-    g.cpl = 32;
-    g.steps = 50;
-    g.wpg = 4;
-    g.halo = 0;
-    return g;
+    // without an entry: 32 cells per lane and 50 steps per pass, for the calls
+    // that give part of the geometry
+    *g = Geom1D{32, 50, 0, 4};
+    if (!tune_lookup(k, &t) || !t.cpl || t.mode != 0) return false;
+    *g = Geom1D{t.cpl, t.steps, 0, t.wpg ? t.wpg : 4};
+    return true;
 }
 
 }  // namespace hx

@@ -10,8 +10,6 @@
 
 namespace hx {
 
-struct Ctx;
-
 struct TuneKey {
     std::string s;
 };
@@ -36,9 +34,8 @@ bool tune_lookup(const TuneKey& k, TunedGeom* g);
 void tune_store(const TuneKey& k, const TunedGeom& g);
 void tune_erase(const TuneKey& k);
 
-// Default 1D geometry for a key: the tuned entry if one exists, otherwise the
-// built-in heuristic.
-Geom1D default_geom_1d(Ctx* c, const TuneKey& k);
+// The tuned 1D geometry of a key (true), else a fixed one (false).
+bool tuned_geom_1d(const TuneKey& k, Geom1D* g);
 
 int max_time_block_1d(int dtype, int cpl);
 
