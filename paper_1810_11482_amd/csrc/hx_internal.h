@@ -89,6 +89,25 @@ std::vector<int> choose_depths1d(int dtype, int64_t n, int steps);
 // dtype: 0 = f32, 1 = f64.  Returns hipSuccess or the launch error.
 hipError_t launch_stencil1d(int dtype, const Seg1D& seg, const Geom1D& g, hipStream_t stream);
 
+// Up to kMaxParts neighbouring partitions of one 1D array advanced by one pass
+// of g.steps steps in one launch: partition p reads its halo cells from the
+// ends of partitions p - 1 and p + 1, the first and the last from halo_lo and
+// halo_hi (g.steps cells, as Seg1D; null: a zero-Dirichlet end).  Every
+// partition has at least g.steps cells.  The set travels as the kernel
+// argument.
+constexpr int kMaxParts = 64;
+struct PartSet1D {
+    const void* in[kMaxParts];
+    void* out[kMaxParts];
+    int64_t n[kMaxParts];
+    const void* halo_lo;
+    const void* halo_hi;
+    double r;
+    int32_t count;
+};
+hipError_t launch_stencil1d_parts(int dtype, const PartSet1D& set, const Geom1D& g,
+                                  hipStream_t stream);
+
 // Batched 1D: segments described in device memory; `ntiles` entries of
 // (segment index, tile index within the segment) in device memory.  With
 // grid_waves >= ntiles (or <= 0) every wave takes one tile, otherwise

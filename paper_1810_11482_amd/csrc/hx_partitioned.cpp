@@ -22,6 +22,7 @@
 
 #include "hx_internal.h"
 #include "hx_runtime.hpp"
+#include "hx_tune.hpp"
 
 using namespace hx;
 
@@ -72,16 +73,20 @@ hx_status run_bands_batched(Ctx* c, const hx_partitioned_desc* d, hx_event gate,
     const int dt = d->dtype == HX_F64 ? 1 : 0;
     const int64_t es = dt ? 8 : 4;
     const int vn = dt ? 2 : 4;
-    // the library's own form and geometry, unless some of it is given
-    const bool choose = !d->cells_per_lane && !d->rows_per_block && !d->waves_per_group;
+    // the library's own form and geometry, unless some of it is given or tuned
+    TunedGeom tg;
+    const bool given = d->cells_per_lane || d->rows_per_block || d->waves_per_group;
+    const int D = d->time_block > 0 ? d->time_block : std::min(d->steps, 8);
+    const bool tuned = !given && tune_lookup(tune_key_2d(dt, d->sizes[0], d->nx, D), &tg) &&
+                       tg.mode == 0 && tg.cpl && tg.rows > 0 && tg.wpg;
+    const bool choose = !given && !tuned;
     Geom2D g;
-    g.cpl = d->cells_per_lane ? d->cells_per_lane : 4;
-    g.rows = d->rows_per_block ? d->rows_per_block : 128;
-    g.wpg = d->waves_per_group ? d->waves_per_group : 4;
+    g.cpl = d->cells_per_lane ? d->cells_per_lane : (tuned ? tg.cpl : 4);
+    g.rows = d->rows_per_block ? d->rows_per_block : (tuned ? tg.rows : 128);
+    g.wpg = d->waves_per_group ? d->waves_per_group : (tuned ? tg.wpg : 4);
     if (g.wpg != 1 && g.wpg != 2 && g.wpg != 4)
         return c->fail(HX_ERR_ARG, "waves_per_group must be 1, 2 or 4");
     if (g.rows < 1) return c->fail(HX_ERR_ARG, "rows_per_block must be positive");
-    const int D = d->time_block > 0 ? d->time_block : std::min(d->steps, 8);
     int64_t min_rows = d->sizes[0];
     for (int p = 1; p < P; ++p) min_rows = std::min(min_rows, d->sizes[p]);
     if (D > min_rows) return c->fail(HX_ERR_ARG, "time_block exceeds the smallest band");
@@ -197,6 +202,120 @@ hx_status run_bands_batched(Ctx* c, const hx_partitioned_desc* d, hx_event gate,
     return s;
 }
 
+// HX_PART_GRAPH over 1D partitions when nobody can see the nodes (no node
+// events, no hazard checker, no injected failure, no capture): every pass is
+// one launch per group of up to kMaxParts partitions, a node per launch,
+// depending on every node of the previous pass.  The same arithmetic as the
+// node form, so the same bits; what it saves is the host work of a node per
+// partition (about 11 us each, more than most partitions' kernels).
+hx_status run_parts_set(Ctx* c, const hx_partitioned_desc* d, int D, hx_event gate, hx_event* out,
+                        int* final_in_b) {
+    const int P = d->parts;
+    const int dt = d->dtype == HX_F64 ? 1 : 0;
+    const int64_t es = dt ? 8 : 4;
+    const int vn = dt ? 2 : 4;
+    const bool choose = !d->cells_per_lane && !d->waves_per_group;
+    Geom1D g{};
+    g.cpl = d->cells_per_lane ? d->cells_per_lane : 32;
+    g.wpg = d->waves_per_group ? d->waves_per_group : 4;
+    if (g.cpl != 8 && g.cpl != 16 && g.cpl != 32 && g.cpl != 64)
+        return c->fail(HX_ERR_ARG, "cells_per_lane must be 8, 16, 32 or 64");
+    if (g.wpg != 1 && g.wpg != 2 && g.wpg != 4)
+        return c->fail(HX_ERR_ARG, "waves_per_group must be 1, 2 or 4");
+    if (D > max_time_block_1d(d->dtype, g.cpl))
+        return c->fail(HX_ERR_ARG, "time_block exceeds the tile limit of the geometry");
+    // addresses and ranges of both buffer sets
+    std::vector<char*> ptr[2];
+    std::vector<Access> acc[2];
+    for (int set = 0; set < 2; ++set)
+        for (int p = 0; p < P; ++p) {
+            char* q = nullptr;
+            Access a{};
+            hx_status s = resolve_range(c, set ? d->bufs_b[p] : d->bufs_a[p], 0,
+                                        (size_t)(d->sizes[p] * es), &q, &a, false);
+            if (s) return s;
+            ptr[set].push_back(q);
+            acc[set].push_back(a);
+        }
+    for (int p = 0; p < P; ++p)
+        if (acc[0][p].buf_slot == acc[1][p].buf_slot)
+            return c->fail(HX_ERR_ARG, "in and out overlap");
+    const int passes = (d->steps + D - 1) / D;
+    std::vector<hx_event> prev, cur;
+    if (gate) {
+        hx_event gcopy = 0;
+        hx_status s = when_all_locked(c, &gate, 1, &gcopy);
+        if (s) return s;
+        prev.push_back(gcopy);
+    }
+    auto drop = [&](std::vector<hx_event>& v) {
+        for (hx_event e : v) release_locked(c, e);
+        v.clear();
+    };
+    int left = d->steps;
+    for (int b = 0; b < passes; ++b) {
+        const int depth = std::min(D, left);
+        const int src = b % 2;
+        left -= depth;
+        for (int p0 = 0; p0 < P; p0 += kMaxParts) {
+            const int count = std::min(kMaxParts, P - p0), p1 = p0 + count;
+            PartSet1D set{};
+            std::vector<Access> use;
+            for (int p = p0; p < p1; ++p) {
+                set.in[p - p0] = ptr[src][p];
+                set.out[p - p0] = ptr[1 - src][p];
+                set.n[p - p0] = d->sizes[p];
+                use.push_back(acc[src][p]);
+                use.push_back(acc[1 - src][p]);
+                use.back().write = true;
+            }
+            const int lp = (p0 + P - 1) % P, rp = p1 % P;
+            if (d->periodic || p0 > 0) {
+                set.halo_lo = ptr[src][lp] + (d->sizes[lp] - depth) * es;
+                use.push_back(acc[src][lp]);
+            }
+            if (d->periodic || p1 < P) {
+                set.halo_hi = ptr[src][rp];
+                use.push_back(acc[src][rp]);
+            }
+            set.r = d->r;
+            set.count = count;
+            Geom1D gg = g;
+            gg.steps = depth;
+            gg.halo = std::max(vn, (depth + vn - 1) / vn * vn);
+            double us;
+            Geom1D tg;
+            if (choose && tuned_geom_1d(tune_key_1d(d->dtype, d->sizes[p0], depth, true), &tg) &&
+                depth <= max_time_block_1d(d->dtype, tg.cpl)) {
+                gg.cpl = tg.cpl;
+                gg.wpg = tg.wpg;
+            } else if (choose && depth <= max_time_block_1d(d->dtype, 16)) {
+                gg = choose_geom1d(dt, d->sizes + p0, count, depth, &us);
+            }
+            hx_event ev = 0;
+            hx_status s = c->submit(
+                SC_COMPUTE, prev.data(), (int)prev.size(), use,
+                "stencil1d pass of " + std::to_string(count) + " partitions",
+                [set, gg, dt](hipStream_t st) -> hipError_t {
+                    return launch_stencil1d_parts(dt, set, gg, st);
+                },
+                &ev);
+            if (s) {
+                drop(prev);
+                drop(cur);
+                return s;
+            }
+            cur.push_back(ev);
+        }
+        drop(prev);
+        prev.swap(cur);
+    }
+    hx_status s = when_all_locked(c, prev.data(), (int)prev.size(), out);
+    drop(prev);
+    if (final_in_b) *final_in_b = (passes % 2 == 1);
+    return s;
+}
+
 }  // namespace
 
 extern "C" hx_status hx_run_partitioned(hx_ctx ctx, const hx_partitioned_desc* d,
@@ -208,7 +327,13 @@ extern "C" hx_status hx_run_partitioned(hx_ctx ctx, const hx_partitioned_desc* d
     if (!out) return c->fail(HX_ERR_ARG, "null output event");
     hx_status s = validate(c, d);
     if (s) return s;
-    if (d->mode == HX_PART_BATCHED) {
+    // a graph whose nodes nobody can see takes its passes whole (a single
+    // partition without halos is an ordinary run, with an ordinary run's rules)
+    const bool unseen = d->mode == HX_PART_GRAPH && !node_events && !c->check && !c->capturing &&
+                        !c->inject_seq && !c->host_only && d->steps > 0 &&
+                        (d->parts > 1 || d->periodic);
+    if (!c->host_only) hipSetDevice(c->device);
+    if (d->mode == HX_PART_BATCHED || (unseen && d->dims == 2)) {
         if (d->dims != 2)
             return c->fail(HX_ERR_ARG, "HX_PART_BATCHED runs 2D bands; 1D batches use "
                                        "hx_plan_create_batched");
@@ -232,6 +357,16 @@ extern "C" hx_status hx_run_partitioned(hx_ctx ctx, const hx_partitioned_desc* d
     int64_t min_size = d->sizes[0];
     for (int p = 1; p < P; ++p) min_size = std::min(min_size, d->sizes[p]);
     if (D > min_size) return c->fail(HX_ERR_ARG, "time_block exceeds the smallest partition");
+    if (unseen) {
+        hx_event g = 0;
+        if (ndeps > 0) {
+            s = when_all_locked(c, deps, ndeps, &g);
+            if (s) return s;
+        }
+        s = run_parts_set(c, d, D, g, out, final_in_b);
+        release_locked(c, g);
+        return s;
+    }
     const int passes = d->steps == 0 ? 0 : (d->steps + D - 1) / D;
     const size_t es = esz(d->dtype);
 

@@ -494,6 +494,38 @@ __global__ __launch_bounds__(256) void k_stencil1d_flat(const Seg1D* __restrict_
     tile1d<T, C, SC>(segs[si], ti, steps, halo, wave_lds<T, C>());
 }
 
+// A pass over neighbouring partitions (PartSet1D) in one launch.  As separate
+// operations each cost about 11 us of host work, more than the kernel of a
+// 2^20-cell partition took; a wave finds its partition by division (`per`, the
+// most tiles a partition has) and a short walk, and builds its segment from
+// the set.
+struct PartTiles {
+    uint32_t first[kMaxParts + 1];  // tiles before partition p
+    uint32_t per;
+};
+
+template <typename T, int C, bool SC>
+__global__ __launch_bounds__(256) void k_stencil1d_parts(PartSet1D ps, PartTiles pt, Seg1D rate,
+                                                         int steps, int halo) {
+    const int wpg = blockDim.x >> 6;
+    const uint32_t t = blockIdx.x * wpg + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (t >= pt.first[ps.count]) return;
+    int p = (int)(t / pt.per);
+    while (t >= pt.first[p + 1]) ++p;
+    Seg1D s = rate;
+    s.in = ps.in[p];
+    s.out = ps.out[p];
+    s.n = ps.n[p];
+    s.halo_lo = p > 0 ? static_cast<const T*>(ps.in[p - 1]) + (ps.n[p - 1] - steps)
+                      : static_cast<const T*>(ps.halo_lo);
+    s.halo_hi = p + 1 < ps.count ? ps.in[p + 1] : ps.halo_hi;
+    s.bc_lo = s.halo_lo ? BC_GHOST : BC_DIRICHLET0;
+    s.bc_hi = s.halo_hi ? BC_GHOST : BC_DIRICHLET0;
+    s.hw = steps;
+    s.shift = (int32_t)((reinterpret_cast<uintptr_t>(s.in) / sizeof(T)) % V16<T>::N);
+    tile1d<T, C, SC>(s, t - pt.first[p], steps, halo, wave_lds<T, C>());
+}
+
 #define HX_CPL_SWITCH(KERNEL, ...)                                                    \
     switch (g.cpl) {                                                                  \
     case 8: hipLaunchKernelGGL((KERNEL<T, 8, SC>), __VA_ARGS__); break;                \
@@ -545,6 +577,35 @@ hipError_t launch_single(const Seg1D& s0, const Geom1D& g, hipStream_t st) {
     s.shift = tile_shift(s.in, sizeof(T));
     set_rate_1d(s, g.steps);
     return s.period > 0 ? launch_single_sc<T, true>(s, g, st) : launch_single_sc<T, false>(s, g, st);
+}
+
+template <typename T, bool SC>
+hipError_t launch_parts_sc(const PartSet1D& set, const Seg1D& rate, const Geom1D& g,
+                           hipStream_t st) {
+    PartTiles pt{};
+    for (int p = 0; p < set.count; ++p) {
+        Seg1D s{};
+        s.n = set.n[p];
+        s.shift = tile_shift(set.in[p], sizeof(T));
+        const int64_t nt = tiles_1d(s, g);
+        if (pt.first[p] + nt >= (int64_t(1) << 31)) return hipErrorInvalidValue;
+        pt.first[p + 1] = pt.first[p] + (uint32_t)nt;
+        pt.per = std::max(pt.per, (uint32_t)nt);
+    }
+    const dim3 block(64 * g.wpg);
+    const dim3 grid((pt.first[set.count] + g.wpg - 1) / g.wpg);
+    const size_t sh = lds_bytes<T>(g);
+    HX_CPL_SWITCH(k_stencil1d_parts, grid, block, sh, st, set, pt, rate, g.steps, g.halo)
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_parts(const PartSet1D& set, const Geom1D& g, hipStream_t st) {
+    Seg1D rate{};
+    rate.r = set.r;
+    set_rate_1d(rate, g.steps);
+    return rate.period > 0 ? launch_parts_sc<T, true>(set, rate, g, st)
+                           : launch_parts_sc<T, false>(set, rate, g, st);
 }
 
 template <typename T, bool SC>
@@ -647,6 +708,12 @@ std::vector<int> choose_depths1d(int dtype, int64_t n, int steps) {
 
 hipError_t launch_stencil1d(int dtype, const Seg1D& seg, const Geom1D& g, hipStream_t stream) {
     return dtype == 0 ? launch_single<float>(seg, g, stream) : launch_single<double>(seg, g, stream);
+}
+
+hipError_t launch_stencil1d_parts(int dtype, const PartSet1D& set, const Geom1D& g,
+                                  hipStream_t stream) {
+    if (set.count < 1 || set.count > kMaxParts || g.steps < 1) return hipErrorInvalidValue;
+    return dtype == 0 ? launch_parts<float>(set, g, stream) : launch_parts<double>(set, g, stream);
 }
 
 hipError_t launch_stencil1d_batched(int dtype, const Seg1D* segs_dev, const uint32_t* tile_seg,
