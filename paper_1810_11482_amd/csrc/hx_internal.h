@@ -83,8 +83,9 @@ inline int64_t tiles_1d(const Seg1D& s, const Geom1D& g) {
 // lines lie); *us receives the pass's modelled time.  depth must fit 16 cells
 // per lane.
 Geom1D choose_geom1d(int dtype, const int64_t* n, int count, int depth, double* us);
-// Pass depths of a run of `steps` steps over n cells, in the library's choice.
-std::vector<int> choose_depths1d(int dtype, int64_t n, int steps);
+// Pass depths of a run of `steps` steps at rate r over n cells, in the
+// library's choice.
+std::vector<int> choose_depths1d(int dtype, double r, int64_t n, int steps);
 
 // dtype: 0 = f32, 1 = f64.  Returns hipSuccess or the launch error.
 hipError_t launch_stencil1d(int dtype, const Seg1D& seg, const Geom1D& g, hipStream_t stream);
@@ -107,6 +108,33 @@ struct PartSet1D {
 };
 hipError_t launch_stencil1d_parts(int dtype, const PartSet1D& set, const Geom1D& g,
                                   hipStream_t stream);
+
+// The propagator form of such a pass (hx_propline.hip; f32): every partition at
+// least kPropLineMin cells.  propline_setup fills what a pass of D steps at
+// rate r needs (host arithmetic of up to 5 us), false where the form does not
+// serve (D over 256, r outside 1e-3 .. 1/4, or 2 r D over about 100).
+constexpr int64_t kPropLineMin = 2048;
+struct PropLine {
+    uint16_t tap[2][192];
+    uint32_t levels;
+    int32_t texp, H, D;
+    float chk;
+};
+bool propline_setup(double r, int D, PropLine* out);
+// Modelled time of such a pass over `cells` cells, us, the setup's host time
+// included; infinite where the form is not taken.
+double propline_us(double r, int64_t cells, int D);
+hipError_t launch_propline(const PartSet1D& set, const PropLine& pl, hipStream_t stream);
+
+// The form and geometry of a pass of `depth` steps over `count` neighbouring
+// runs of n[i] cells, in the library's choice: prop set and pl filled, or the
+// direct form's g.
+struct Pass1D {
+    bool prop;
+    Geom1D g;
+    PropLine pl;
+};
+Pass1D choose_pass1d(int dtype, double r, const int64_t* n, int count, int depth);
 
 // Batched 1D: segments described in device memory; `ntiles` entries of
 // (segment index, tile index within the segment) in device memory.  With

@@ -205,9 +205,10 @@ hx_status run_bands_batched(Ctx* c, const hx_partitioned_desc* d, hx_event gate,
 // HX_PART_GRAPH over 1D partitions when nobody can see the nodes (no node
 // events, no hazard checker, no injected failure, no capture): every pass is
 // one launch per group of up to kMaxParts partitions, a node per launch,
-// depending on every node of the previous pass.  The same arithmetic as the
-// node form, so the same bits; what it saves is the host work of a node per
-// partition (about 11 us each, more than most partitions' kernels).
+// depending on every node of the previous pass.  What it saves is the host work
+// of a node per partition (about 11 us each, more than most partitions'
+// kernels).  The same arithmetic as the node form, so the same bits, unless a
+// f32 pass takes the propagator form (agreement to rounding).
 hx_status run_parts_set(Ctx* c, const hx_partitioned_desc* d, int D, hx_event gate, hx_event* out,
                         int* final_in_b) {
     const int P = d->parts;
@@ -280,24 +281,27 @@ hx_status run_parts_set(Ctx* c, const hx_partitioned_desc* d, int D, hx_event ga
             }
             set.r = d->r;
             set.count = count;
-            Geom1D gg = g;
-            gg.steps = depth;
-            gg.halo = std::max(vn, (depth + vn - 1) / vn * vn);
-            double us;
+            Pass1D how{};
+            how.g = g;
+            how.g.steps = depth;
+            how.g.halo = std::max(vn, (depth + vn - 1) / vn * vn);
             Geom1D tg;
             if (choose && tuned_geom_1d(tune_key_1d(d->dtype, d->sizes[p0], depth, true), &tg) &&
                 depth <= max_time_block_1d(d->dtype, tg.cpl)) {
-                gg.cpl = tg.cpl;
-                gg.wpg = tg.wpg;
+                how.g.cpl = tg.cpl;
+                how.g.wpg = tg.wpg;
             } else if (choose && depth <= max_time_block_1d(d->dtype, 16)) {
-                gg = choose_geom1d(dt, d->sizes + p0, count, depth, &us);
+                how = choose_pass1d(dt, d->r, d->sizes + p0, count, depth);
+                for (int k = 0; k < count; ++k)
+                    if (((uintptr_t)set.in[k] | (uintptr_t)set.out[k]) % es) how.prop = false;
             }
             hx_event ev = 0;
             hx_status s = c->submit(
                 SC_COMPUTE, prev.data(), (int)prev.size(), use,
                 "stencil1d pass of " + std::to_string(count) + " partitions",
-                [set, gg, dt](hipStream_t st) -> hipError_t {
-                    return launch_stencil1d_parts(dt, set, gg, st);
+                [set, how, dt](hipStream_t st) -> hipError_t {
+                    return how.prop ? launch_propline(set, how.pl, st)
+                                    : launch_stencil1d_parts(dt, set, how.g, st);
                 },
                 &ev);
             if (s) {

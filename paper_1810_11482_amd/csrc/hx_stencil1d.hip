@@ -25,8 +25,10 @@
 
 #include <algorithm>
 #include <cmath>
+#include <limits>
 
 #include "hx_internal.h"
+#include "hx_line.hpp"
 
 namespace hx {
 namespace {
@@ -38,25 +40,6 @@ typedef double f64x2 __attribute__((ext_vector_type(2)));
 template <typename T> struct V16;
 template <> struct V16<float> { typedef f32x4 t; enum { N = 4 }; };
 template <> struct V16<double> { typedef f64x2 t; enum { N = 2 }; };
-
-// DPP controls of the wave-wide shifts: lane i reads lane i-1 (shr) or i+1 (shl);
-// the lane with no source reads 0.
-constexpr int DPP_WAVE_SHL1 = 0x130;
-constexpr int DPP_WAVE_SHR1 = 0x138;
-
-template <int CTRL>
-__device__ __forceinline__ float dpp_move(float x) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp_move(double x) {
-    int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xf, 0xf, true);
-    int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xf, 0xf, true);
-    return __hiloint2double(hi, lo);
-}
-
-__device__ __forceinline__ float fmaT(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ __forceinline__ double fmaT(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
 // Value of cell g (any integer) of segment s at the start of the pass.
 template <typename T>
@@ -81,67 +64,6 @@ __device__ __forceinline__ T load_cell(const Seg1D& s, int64_t g) {
     if (s.bc_hi == BC_GHOST && g - s.n < (int64_t)s.hw)
         return static_cast<const T*>(s.halo_hi)[g - s.n];
     return T(0);
-}
-
-// One step of a whole wave tile, in place on the lane-contiguous registers a.
-// The cell left of a lane's first comes from the lane below, the cell right of
-// its last from the lane above (DPP wave shifts of the old values).  The
-// neighbour sum of cell j+1 is formed from the old a[j] before a[j] is
-// overwritten, so one array and two short-lived temporaries suffice and the
-// register assignment is the same after every step (no register moves).  Per
-// cell: s = l + rt; d = fma(-2, c, s); c' = fma(r, d, c).  Cells outside a
-// zero-Dirichlet end are reset to 0 after the step.
-template <typename T, int C>
-__device__ __forceinline__ void step_tile(T (&a)[C], T k, bool zero_lo, bool zero_hi,
-                                          int64_t lbase, int64_t n) {
-    const T left = dpp_move<DPP_WAVE_SHR1>(a[C - 1]);
-    const T right = dpp_move<DPP_WAVE_SHL1>(a[0]);
-    T s_cur = left + (C > 1 ? a[1] : right);
-#pragma unroll
-    for (int j = 0; j < C; ++j) {
-        T s_next = T(0);
-        if (j + 1 < C) s_next = a[j] + (j + 2 < C ? a[j + 2] : right);
-        const T d = fmaT(T(-2), a[j], s_cur);
-        a[j] = fmaT(k, d, a[j]);
-        s_cur = s_next;
-    }
-    if (zero_lo || zero_hi) {
-#pragma unroll
-        for (int j = 0; j < C; ++j) {
-            const int64_t g = lbase + j;
-            if ((zero_lo && g < 0) || (zero_hi && g >= n)) a[j] = T(0);
-        }
-    }
-}
-
-// One step of the rescaled form (see set_rate_1d): w' = w + b (w_l + w_r).
-// Same register discipline as step_tile: one add and one fma per cell.
-template <typename T, int C>
-__device__ __forceinline__ void step_tile_scaled(T (&a)[C], T b, bool zero_lo, bool zero_hi,
-                                                 int64_t lbase, int64_t n) {
-    const T left = dpp_move<DPP_WAVE_SHR1>(a[C - 1]);
-    const T right = dpp_move<DPP_WAVE_SHL1>(a[0]);
-    T s_cur = left + (C > 1 ? a[1] : right);
-#pragma unroll
-    for (int j = 0; j < C; ++j) {
-        T s_next = T(0);
-        if (j + 1 < C) s_next = a[j] + (j + 2 < C ? a[j + 2] : right);
-        a[j] = fmaT(b, s_cur, a[j]);
-        s_cur = s_next;
-    }
-    if (zero_lo || zero_hi) {
-#pragma unroll
-        for (int j = 0; j < C; ++j) {
-            const int64_t g = lbase + j;
-            if ((zero_lo && g < 0) || (zero_hi && g >= n)) a[j] = T(0);
-        }
-    }
-}
-
-template <typename T, int C>
-__device__ __forceinline__ void scale_tile(T (&a)[C], T f) {
-#pragma unroll
-    for (int j = 0; j < C; ++j) a[j] *= f;
 }
 
 // Segment pointers arrive as generic addresses; the tile's vector accesses go
@@ -684,16 +606,21 @@ Geom1D choose_geom1d(int dtype, const int64_t* n, int count, int depth, double* 
     return g;
 }
 
-std::vector<int> choose_depths1d(int dtype, int64_t n, int steps) {
-    // np passes as even as they can be, np by the least modelled time
+std::vector<int> choose_depths1d(int dtype, double r, int64_t n, int steps) {
+    // np passes as even as they can be, np by the least modelled time, each
+    // pass in the form that is modelled the faster
     int best = 0;
     double best_us = 0.0;
-    for (int np = (steps + kLineDepth - 1) / kLineDepth; np <= (steps + 4) / 5; ++np) {
+    auto pass_us = [&](int d) {
+        double us = std::numeric_limits<double>::infinity();
+        if (d <= kLineDepth) choose_geom1d(dtype, &n, 1, d, &us);
+        return dtype ? us : std::min(us, propline_us(r, n, d));
+    };
+    for (int np = (steps + 255) / 256; np <= (steps + 4) / 5; ++np) {
         const int d = steps / np, more = steps % np;
-        double us = 0.0, us1 = 0.0;
-        choose_geom1d(dtype, &n, 1, d, &us);
-        if (more) choose_geom1d(dtype, &n, 1, d + 1, &us1);
-        const double t = (np - more) * us + more * us1;
+        const double us = pass_us(d), us1 = more ? pass_us(d + 1) : 0.0;
+        const double t = (np - more) * us + (more ? more * us1 : 0.0);
+        if (std::isinf(t)) continue;
         if (best == 0 || t < best_us) {
             best = np;
             best_us = t;
@@ -704,6 +631,20 @@ std::vector<int> choose_depths1d(int dtype, int64_t n, int steps) {
     std::vector<int> plan;
     for (int p = 0; p < best; ++p) plan.push_back(steps / best + (p < steps % best ? 1 : 0));
     return plan;
+}
+
+Pass1D choose_pass1d(int dtype, double r, const int64_t* n, int count, int depth) {
+    Pass1D p{};
+    double us = std::numeric_limits<double>::infinity();
+    p.g = choose_geom1d(dtype, n, count, depth, &us);
+    int64_t cells = 0, least = n[0];
+    for (int k = 0; k < count; ++k) {
+        cells += n[k];
+        least = std::min(least, n[k]);
+    }
+    if (dtype == 0 && least >= kPropLineMin && propline_us(r, cells, depth) < us)
+        p.prop = propline_setup(r, depth, &p.pl);
+    return p;
 }
 
 hipError_t launch_stencil1d(int dtype, const Seg1D& seg, const Geom1D& g, hipStream_t stream) {

@@ -23,6 +23,24 @@ int max_time_block_1d(int dtype, int cpl) {
     return (64 * cpl - vn) / 2 / vn * vn;
 }
 
+// The propagator form of a pass over one line (f32).
+static hipError_t launch_prop_pass(const Seg1D& s, const PropLine& pl, hipStream_t st) {
+    const float* in = static_cast<const float*>(s.in);
+    auto edge = [&](int bc, const float* wrap, const void* halo, int skip) -> const void* {
+        if (bc == HX_BC_PERIODIC) return wrap;
+        return bc == HX_BC_GHOST ? static_cast<const float*>(halo) + skip : nullptr;
+    };
+    PartSet1D set{};
+    set.in[0] = in;
+    set.out[0] = s.out;
+    set.n[0] = s.n;
+    set.halo_lo = edge(s.bc_lo, in + (s.n - pl.D), s.halo_lo, s.hw - pl.D);
+    set.halo_hi = edge(s.bc_hi, in, s.halo_hi, 0);
+    set.r = s.r;
+    set.count = 1;
+    return launch_propline(set, pl, st);
+}
+
 static hx_status launch_1d(Ctx* c, const hx_stencil_args* a, const hx_event* deps, int ndeps,
                            hx_event* out) {
     const int dt = a->dtype;
@@ -93,7 +111,7 @@ static hx_status launch_1d(Ctx* c, const hx_stencil_args* a, const hx_event* dep
     // (a run of more than one pass of time_block steps, or of 50, needs tmp
     // whatever depths are chosen)
     const bool need_tmp = plan.size() > 1;
-    if (choose && !a->time_block && need_tmp) plan = choose_depths1d(dt, n, a->steps);
+    if (choose && !a->time_block && need_tmp) plan = choose_depths1d(dt, a->r, n, a->steps);
     const int passes = (int)plan.size();
     if (need_tmp) {
         if (a->tmp == 0)
@@ -115,14 +133,20 @@ static hx_status launch_1d(Ctx* c, const hx_stencil_args* a, const hx_event* dep
     seg.halo_lo = plo;
     seg.halo_hi = phi;
     const int vn = vec_cells(dt);
-    std::vector<Geom1D> geoms;
+    const bool cell_aligned = (((uintptr_t)pin | (uintptr_t)pout | (uintptr_t)ptmp |
+                                (uintptr_t)plo | (uintptr_t)phi) & (es - 1)) == 0;
+    std::vector<Pass1D> how;
     for (int d : plan) {
-        double us;
-        Geom1D gg = g;
-        gg.steps = d;
-        gg.halo = std::max(vn, round_up(d, vn));
-        geoms.push_back(choose && d <= max_time_block_1d(dt, 16) ? choose_geom1d(dt, &n, 1, d, &us)
-                                                                  : gg);
+        Pass1D ps{};
+        if (choose && d <= max_time_block_1d(dt, 16)) {
+            ps = choose_pass1d(dt, a->r, &n, 1, d);
+            ps.prop = ps.prop && cell_aligned;
+        } else {
+            ps.g = g;
+            ps.g.steps = d;
+            ps.g.halo = std::max(vn, round_up(d, vn));
+        }
+        how.push_back(ps);
     }
     std::string what = "stencil1d n=" + std::to_string(n) + " steps=" + std::to_string(a->steps);
     return c->submit(
@@ -135,7 +159,8 @@ static hx_status launch_1d(Ctx* c, const hx_stencil_args* a, const hx_event* dep
                 Seg1D sg = seg;
                 sg.in = src;
                 sg.out = dst;
-                hipError_t e = launch_stencil1d(dt, sg, geoms[p], st);
+                hipError_t e = how[p].prop ? launch_prop_pass(sg, how[p].pl, st)
+                                           : launch_stencil1d(dt, sg, how[p].g, st);
                 if (e != hipSuccess) return e;
                 src = dst;
             }

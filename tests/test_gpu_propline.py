@@ -1,0 +1,150 @@
+"""The propagator pass that deep f32 passes over one line or over a partitioned
+line take when their geometry is left to the library (blocks of 1024 cells on
+the matrix cores, four to a workgroup), against the oracle: the shortest line
+it takes, block and workgroup edges, any alignment, every boundary, depths on
+both sides of its 64-cell window up to the deepest, runs of several passes, and
+cells its accuracy check hands to stepping (lone values among zeros, large
+values in noise, non-finite cells).
+
+Tolerance of a cell after D steps: stepping rounds three times a step, each
+within 2^-24 of what the cells' magnitudes evolve to, so 3 D 2^-24 of that; the
+propagator's own error (split cells and taps, some 30 sums) is below 2^-19, or
+D = 20.  At a zero end the magnitudes include the line's reflection, which the
+propagator sums over."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+from conftest import rel_l2
+
+pytestmark = pytest.mark.gpu
+hx = pytest.importorskip("paper_1810_11482_amd")
+from hxutil import download, run, upload  # noqa: E402
+
+PER, ZERO, GHOST = hx.HX_BC_PERIODIC, hx.HX_BC_DIRICHLET0, hx.HX_BC_GHOST
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    if hx.hx_device_count() == 0:
+        pytest.skip("no GPU")
+    hx.hx_tune_cache_clear()
+    c = hx.hx_ctx_create(0)
+    yield c
+    hx.hx_ctx_destroy(c)
+
+
+def line(ctx, u0, r, steps, bc, shift=(0, 0), halo=None, **kw):
+    si, so = shift
+    src = upload(ctx, np.concatenate([np.zeros(si, u0.dtype), u0]))
+    out = upload(ctx, np.full(u0.size + so + 64, 7.0, np.float32))
+    tmp = hx.hx_buffer_create(ctx, u0.nbytes + 4 * so)
+    bufs = [src, out, tmp]
+    if halo is not None:
+        lo, hi = (upload(ctx, h) for h in halo)
+        bufs += [lo, hi]
+        kw.update(halo_lo=lo, halo_hi=hi, halo_width=halo[0].size)
+    run(ctx, hx.stencil_args(dims=1, dtype=hx.HX_F32, nx=u0.size, steps=steps, r=r, inp=src,
+                             out=out, tmp=tmp, bc_lo=bc, bc_hi=bc, in_offset=4 * si,
+                             out_offset=4 * so, tmp_offset=4 * so, **kw))
+    res = download(ctx, out, u0.size + so + 64, np.float32)
+    for b in bufs:
+        hx.hx_buffer_destroy(ctx, b)
+    assert np.all(res[:so] == 7.0) and np.all(res[so + u0.size:] == 7.0)
+    return res[so:so + u0.size]
+
+
+def check(got, u0, r, steps, bc, halo=None):
+    """got against the oracle, each cell in the scale of its magnitudes."""
+    u, n = u0.astype(np.float64), u0.size
+    with np.errstate(all="ignore"):
+        if bc == PER:
+            ref, scale = (oracle.heat1d_periodic(x, r, steps) for x in (u, np.abs(u)))
+        else:
+            if bc == GHOST:
+                ext = np.concatenate([halo[0][-steps:], u, halo[1][:steps]]).astype(np.float64)
+                at = steps
+            else:
+                z = np.zeros(1)
+                ext, at = np.concatenate([-u[::-1], z, u, z, -u[::-1]]), n + 1
+            ref, scale = (oracle.heat1d_periodic(x, r, steps)[at:at + n]
+                          for x in (ext, np.abs(ext)))
+        fin = np.isfinite(ref)
+        assert np.array_equal(fin, np.isfinite(got))
+        err = np.abs(got - ref)[fin]
+    tol = 3 * max(steps, 20) * 2.0 ** -24 * scale[fin] + 2.0 ** -124
+    assert np.all(err <= tol), (np.max(err / tol), int(np.argmax(err / tol)))
+
+
+def field(kind, n, seed):
+    u = workloads.uniform(n, 950, seed, 0, 1, np.float32)
+    if kind == "signed":
+        u = 2 * u - 1
+    elif kind == "lone":
+        u[:] = 0
+        u[[0, n // 3, n - 1]] = 1.0, 2.0, -1.0
+    elif kind == "spike":
+        u[n // 2], u[3] = 1e20, -1e15
+    elif kind == "nan":
+        u[n // 2], u[n - 5] = np.nan, np.inf
+    return u
+
+
+@pytest.mark.parametrize("bc", [PER, ZERO, GHOST])
+@pytest.mark.parametrize("n", [2048, 2049, 3071, 4096, 4127, 8191, 20011])
+def test_short_lines(ctx, bc, n):
+    g = np.random.default_rng(n)
+    for steps, r in ((80, 0.25), (100, 0.1), (200, 0.25), (256, 0.2)):
+        if bc != GHOST and steps == 256:
+            continue  # two passes of 128, below
+        for k, kind in enumerate(("uniform", "signed", "lone", "spike", "nan")):
+            u0 = field(kind, n, steps)
+            halo = None
+            if bc == GHOST:
+                halo = [g.random(steps + 3 * k).astype(np.float32) for _ in range(2)]
+            got = line(ctx, u0, r, steps, bc, shift=((k + 1) % 4, (7 * k + n) % 33), halo=halo,
+                       time_block=0 if bc == GHOST else steps)
+            check(got, u0, r, steps, bc, halo)
+            if kind == "uniform" and steps >= 100:  # this form, not the stepping one
+                direct = line(ctx, u0, r, steps, bc, halo=halo, cells_per_lane=16,
+                              time_block=steps)
+                assert not np.array_equal(got, direct)
+
+
+@pytest.mark.parametrize("bc", [PER, ZERO])
+@pytest.mark.parametrize("steps,r", [(20, 0.25), (29, 0.05), (50, 0.25), (64, 0.2), (65, 0.15)])
+def test_long_lines_every_window(ctx, bc, steps, r):
+    u0 = field("signed", 1500007, steps)
+    got = line(ctx, u0, r, steps, bc, shift=(steps % 4, steps % 31))
+    check(got, u0, r, steps, bc)
+
+
+@pytest.mark.parametrize("n,steps,r", [(5003, 256, 0.2), (5003, 1000, 0.25), (70001, 333, 0.24)])
+def test_several_passes(ctx, n, steps, r):
+    u0 = field("uniform", n, steps)
+    for bc in (PER, ZERO):
+        got = line(ctx, u0, r, steps, bc, shift=(1, 2))
+        check(got, u0, r, steps, bc)
+
+
+@pytest.mark.parametrize("periodic", [True, False])
+@pytest.mark.parametrize("sizes", [[2048, 2049, 5000, 2048], [40000 + 13 * k for k in range(70)]])
+def test_partitions(ctx, periodic, sizes):
+    n, steps, tb, r = sum(sizes), 150, 100, 0.25
+    u0 = field("signed", n, len(sizes))
+    off = np.cumsum([0] + sizes)
+    raw = [upload(ctx, np.concatenate([np.zeros(3, np.float32), u0])),
+           hx.hx_buffer_create(ctx, u0.nbytes + 12)]
+    sets = [[hx.hx_buffer_wrap(ctx, hx.hx_buffer_ptr(ctx, b)[0] + 12 + 4 * int(o), 4 * m)
+             for o, m in zip(off, sizes)] for b in raw]
+    d = hx.partitioned_desc(hx.HX_F32, sizes, *sets, steps, r, periodic=periodic, time_block=tb)
+    ev, in_b, _ = hx.hx_run_partitioned(ctx, d)
+    assert hx.hx_wait(ctx, ev) == hx.HX_OK, hx.hx_last_error(ctx)
+    hx.hx_event_release(ctx, ev)
+    got = download(ctx, raw[int(in_b)], n, np.float32, offset=12)
+    for b in sets[0] + sets[1] + raw:
+        hx.hx_buffer_destroy(ctx, b)
+    check(got, u0, r, steps, PER if periodic else ZERO)
+    f = oracle.heat1d_periodic if periodic else oracle.heat1d_dirichlet
+    assert rel_l2(got, f(u0.astype(np.float64), r, steps)) <= 1e-5
