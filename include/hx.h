@@ -297,7 +297,9 @@ typedef enum {
                                   cores (f32 only); the plan fails with HX_ERR_ARG unless every
                                   segment qualifies, see hx_plan_create_batched */
     HX_FORM_AUTO = 2           /* the tuned form, else PROPAGATOR where every segment qualifies,
-                                  else DIRECT */
+                                  else the faster by the library's model of DIRECT and, for
+                                  f32, a propagator pass for segments of any size, alignment
+                                  and boundary (the same accuracy and checks) */
 } hx_batch_form;
 
 typedef struct {

@@ -59,6 +59,10 @@ struct BatchPlan {
     int pwpg = 1;
     int64_t pblocks = 0;   // interleaved: 1024-cell blocks in all, and per segment
     int64_t pbps = 0;
+    LineSeg* lsegs_dev = nullptr;  // line propagator pass: the segments, each
+    uint32_t* lwg_dev = nullptr;   // workgroup's segment,
+    int64_t lwgs = 0, lcells = 0;  // how many, their cells
+    int lH = 0;                    // and the half window
     hipStream_t cap = nullptr;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -80,6 +84,8 @@ void destroy_plan(void* p) {
     if (b->pwaves_dev) hipFree(b->pwaves_dev);
     if (b->taps_dev) hipFree(b->taps_dev);
     if (b->ptab_dev) hipFree(b->ptab_dev);
+    if (b->lsegs_dev) hipFree(b->lsegs_dev);
+    if (b->lwg_dev) hipFree(b->lwg_dev);
     delete b;
 }
 
@@ -121,6 +127,59 @@ const char* prop_unfit(const Seg1D& s, int D) {
     if (!aligned16(lo_end) || !aligned16(s.halo_hi))
         return "the end of halo_lo and the start of halo_hi must be 16-byte aligned";
     return nullptr;
+}
+
+// The segments of a line propagator pass of D steps (hx_propline.hip), or none
+// where some segment does not qualify or the pass is modelled slower than
+// `direct_us`.  Small segments leave waves of their workgroups idle (each is
+// counted as half a workgroup's cells at least), and each segment's first
+// workgroups wait for its description (5 ns).
+std::vector<LineSeg> line_segments(const std::vector<Seg1D>& segs, int D, double direct_us) {
+    int64_t cells = 0, wgs = 0;
+    double rmax = 0.0;
+    for (const Seg1D& s : segs) {
+        const uintptr_t at = reinterpret_cast<uintptr_t>(s.in) |
+                             reinterpret_cast<uintptr_t>(s.out) |
+                             reinterpret_cast<uintptr_t>(s.halo_lo) |
+                             reinterpret_cast<uintptr_t>(s.halo_hi);
+        if (s.n < kPropLineMin || at % 4) return {};
+        const int64_t wg = propline_wgs(s.out, s.n);
+        cells += std::max(s.n, 2048 * wg);
+        wgs += wg;
+        rmax = std::max(rmax, s.r);
+    }
+    const double us = propline_us(rmax, cells, D, false) + 0.005 * (double)segs.size();
+    if (wgs >= (int64_t(1) << 24) || !(us < direct_us)) return {};
+    // the widest window serves all; a rate's taps are computed once
+    std::map<double, PropLine> by_rate;
+    int H = 0;
+    for (const Seg1D& s : segs) {
+        PropLine& pl = by_rate[s.r];
+        if (pl.D) continue;
+        if (!propline_setup(s.r, D, &pl)) return {};
+        H = std::max(H, pl.H);
+    }
+    for (auto& kv : by_rate)
+        if (kv.second.H != H && !propline_setup(kv.first, D, &kv.second, H)) return {};
+    std::vector<LineSeg> ls;
+    uint32_t first = 0;
+    for (const Seg1D& s : segs) {
+        LineSeg q{};
+        q.in = static_cast<const float*>(s.in);
+        q.out = static_cast<float*>(s.out);
+        q.n = s.n;
+        q.hw = s.bc_lo == HX_BC_PERIODIC ? D : s.hw;
+        if (s.bc_lo != HX_BC_DIRICHLET0)
+            q.lo = s.bc_lo == HX_BC_PERIODIC ? q.in + (s.n - D)
+                                             : static_cast<const float*>(s.halo_lo);
+        if (s.bc_hi != HX_BC_DIRICHLET0)
+            q.hi = s.bc_hi == HX_BC_PERIODIC ? q.in : static_cast<const float*>(s.halo_hi);
+        q.first = first;
+        q.pl = by_rate[s.r];
+        first += (uint32_t)propline_wgs(s.out, s.n);
+        ls.push_back(q);
+    }
+    return ls;
 }
 
 // Blocks per wave: the span that fills the device in whole rounds of
@@ -179,7 +238,9 @@ extern "C" hx_status hx_plan_create_batched(hx_ctx ctx, const hx_batch_desc* d, 
     int64_t total = 0;
     for (int i = 0; i < d->count; ++i) total += d->segs[i].n;
     TunedGeom tg;
-    const bool tuned = tune_lookup(tune_key_batched(d->dtype, total, d->count, d->steps), &tg);
+    // (mode 1 + AUTO: tuned, and the library's own choice below was the fastest)
+    const bool tuned = tune_lookup(tune_key_batched(d->dtype, total, d->count, d->steps), &tg) &&
+                       tg.mode != 1 + HX_FORM_AUTO;
     bp->g.cpl = d->cells_per_lane ? d->cells_per_lane : (tuned && tg.cpl ? tg.cpl : 16);
     bp->g.wpg = d->waves_per_group ? d->waves_per_group : (tuned && tg.wpg ? tg.wpg : 4);
     if (bp->g.cpl != 8 && bp->g.cpl != 16 && bp->g.cpl != 32 && bp->g.cpl != 64) {
@@ -272,6 +333,23 @@ extern "C" hx_status hx_plan_create_batched(hx_ctx ctx, const hx_batch_desc* d, 
         }
         const bool tuned_direct = tuned && tg.mode == 1 + HX_FORM_DIRECT;
         bp->prop = !why && !(d->form == HX_FORM_AUTO && tuned_direct);
+    }
+    // untuned, with no geometry given: the tile geometry of the direct form by
+    // modelled time, and for AUTO the line propagator pass where it is faster
+    // (batches the walks above do not take).  Measured, line pass against the
+    // best direct geometry: 4096 periodic segments of 1024 to 2^20 cells at
+    // rates of their own, 20 steps 855 / 977 us; 64 of 2^20 + 1 cells, 50 steps
+    // 99 / 172, 20 steps 93 / 96; 1000 of 1000 to 30000, 50 steps 21 / 28;
+    // 4096 of 256 to 1024, 20 steps a tie at 14.
+    std::vector<LineSeg> lsegs;
+    if (!bp->prop && !tuned && d->mode == HX_BATCH_PERSISTENT && !d->cells_per_lane &&
+        !d->waves_per_group && !d->grid_waves_per_cu && fused <= max_time_block_1d(d->dtype, 16)) {
+        std::vector<int64_t> sizes;
+        for (const Seg1D& sg : bp->segs) sizes.push_back(sg.n);
+        double us = 0.0;
+        bp->g = choose_geom1d(d->dtype == HX_F64 ? 1 : 0, sizes.data(), d->count, fused, &us);
+        if (d->form == HX_FORM_AUTO && d->dtype == HX_F32 && d->span_blocks == 0)
+            lsegs = line_segments(bp->segs, fused, us);
     }
     if (!bp->prop && fused > max_time_block_1d(d->dtype, bp->g.cpl)) {
         delete bp;
@@ -439,6 +517,24 @@ extern "C" hx_status hx_plan_create_batched(hx_ctx ctx, const hx_batch_desc* d, 
             destroy_plan(bp);
             return c->fail(HX_ERR_OOM, "could not allocate the propagator tables");
         }
+    } else if (!lsegs.empty()) {
+        std::vector<uint32_t> wg;
+        for (size_t i = 0; i < lsegs.size(); ++i) {
+            wg.resize(wg.size() + propline_wgs(lsegs[i].out, lsegs[i].n), (uint32_t)i);
+            bp->lcells += lsegs[i].n;
+        }
+        bp->lwgs = (int64_t)wg.size();
+        bp->lH = lsegs[0].pl.H;
+        const size_t sb = sizeof(LineSeg) * lsegs.size();
+        if (hipMalloc(&bp->lsegs_dev, sb) != hipSuccess ||
+            hipMalloc(&bp->lwg_dev, 4 * wg.size()) != hipSuccess ||
+            hipMemcpy(bp->lsegs_dev, lsegs.data(), sb, hipMemcpyHostToDevice) != hipSuccess ||
+            hipMemcpy(bp->lwg_dev, wg.data(), 4 * wg.size(), hipMemcpyHostToDevice) !=
+                hipSuccess) {
+            hipGetLastError();
+            destroy_plan(bp);
+            return c->fail(HX_ERR_OOM, "could not allocate the batch tables");
+        }
     } else if (d->mode == HX_BATCH_PERSISTENT) {
         // tile table, largest segments first
         std::vector<int> order(d->count);
@@ -544,6 +640,9 @@ extern "C" hx_status hx_launch_batched(hx_ctx ctx, hx_plan plan, const hx_event*
             if (bp->prop)
                 return launch_prop1d(bp->psegs_dev, bp->pwaves_dev, bp->pwaves, bp->steps,
                                      bp->pskip, st);
+            if (bp->lwgs)
+                return launch_propline_batch(bp->lsegs_dev, bp->lwg_dev, bp->lwgs, bp->lcells,
+                                             bp->lH, st);
             if (bp->mode == HX_BATCH_PERSISTENT)
                 return launch_stencil1d_batched(bp->dtype, bp->segs_dev, bp->tseg_dev,
                                                 bp->tidx_dev, bp->ntiles, bp->g, bp->grid_waves,

@@ -111,30 +111,53 @@ hipError_t launch_stencil1d_parts(int dtype, const PartSet1D& set, const Geom1D&
 
 // The propagator form of such a pass (hx_propline.hip; f32): every partition at
 // least kPropLineMin cells.  propline_setup fills what a pass of D steps at
-// rate r needs (host arithmetic of up to 5 us), false where the form does not
-// serve (D over 256, r outside 1e-3 .. 1/4, or 2 r D over about 100).
-constexpr int64_t kPropLineMin = 2048;
+// rate r needs (host arithmetic of up to 5 us), with a half window of at least
+// min_H cells, false where the form does not serve (D over 256, r outside 1e-3
+// .. 1/4, or 2 r D over about 100).
+constexpr int64_t kPropLineMin = 256;
 struct PropLine {
-    uint16_t tap[2][192];
-    uint32_t levels;
+    uint16_t tap[2][192];  // level (hi, lo) of tap j = -H - 31 + k, scaled by 2^texp
+    uint32_t levels;       // products per window chunk, as prop1d_levels16
     int32_t texp, H, D;
-    float chk;
+    float chk;             // 2^21 E 2^texp: the check's threshold per unit of |x| in reach
+    float beta, ap, ar;    // the stepping path's rescaled update (Seg1D)
+    int32_t period;
 };
-bool propline_setup(double r, int D, PropLine* out);
-// Modelled time of such a pass over `cells` cells, us, the setup's host time
-// included; infinite where the form is not taken.
-double propline_us(double r, int64_t cells, int D);
+bool propline_setup(double r, int D, PropLine* out, int min_H = 0);
+// Modelled time of such a pass over `cells` cells, us; infinite where the form
+// is not taken.  setup: with propline_setup's host time.
+double propline_us(double r, int64_t cells, int D, bool setup = true);
 hipError_t launch_propline(const PartSet1D& set, const PropLine& pl, hipStream_t stream);
+
+// The same pass over a batch of segments of their own sizes, rates and ends,
+// described in device memory with `nwg` workgroups: workgroup w takes cells
+// 4096 (w - first) .. of segment wg_seg[w] (propline_wgs workgroups each, from
+// a 128-byte line of `out` on).  Every segment's H is `H`.
+struct LineSeg {
+    const float* in;
+    float* out;
+    int64_t n;
+    const float* lo;  // hw cells before the first, or null: a zero-Dirichlet end
+    const float* hi;  // hw cells after the last, or null
+    int32_t hw;
+    uint32_t first;   // workgroups before this segment's
+    PropLine pl;
+};
+inline int64_t propline_wgs(const void* out, int64_t n) {
+    return (n + ((reinterpret_cast<uintptr_t>(out) >> 2) & 31) + 4095) / 4096;
+}
+hipError_t launch_propline_batch(const LineSeg* segs_dev, const uint32_t* wg_seg_dev, int64_t nwg,
+                                 int64_t cells, int H, hipStream_t stream);
 
 // The form and geometry of a pass of `depth` steps over `count` neighbouring
 // runs of n[i] cells, in the library's choice: prop set and pl filled, or the
-// direct form's g.
+// direct form's g.  fed: a run or partition whose halos are given.
 struct Pass1D {
     bool prop;
     Geom1D g;
     PropLine pl;
 };
-Pass1D choose_pass1d(int dtype, double r, const int64_t* n, int count, int depth);
+Pass1D choose_pass1d(int dtype, double r, const int64_t* n, int count, int depth, bool fed);
 
 // Batched 1D: segments described in device memory; `ntiles` entries of
 // (segment index, tile index within the segment) in device memory.  With

@@ -291,7 +291,7 @@ hx_status run_parts_set(Ctx* c, const hx_partitioned_desc* d, int D, hx_event ga
                 how.g.cpl = tg.cpl;
                 how.g.wpg = tg.wpg;
             } else if (choose && depth <= max_time_block_1d(d->dtype, 16)) {
-                how = choose_pass1d(dt, d->r, d->sizes + p0, count, depth);
+                how = choose_pass1d(dt, d->r, d->sizes + p0, count, depth, true);
                 for (int k = 0; k < count; ++k)
                     if (((uintptr_t)set.in[k] | (uintptr_t)set.out[k]) % es) how.prop = false;
             }

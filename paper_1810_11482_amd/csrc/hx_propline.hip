@@ -1,4 +1,5 @@
-// Propagator pass over neighbouring partitions of a line (f32), for gfx950:
+// Propagator pass over neighbouring partitions of a line, or over a batch of
+// segments of any sizes and rates (f32), for gfx950:
 // the form of hx_prop1d.hip's block walk for lines of any length, alignment
 // and boundary, at depths up to 256 steps, with nothing laid out beforehand.
 //
@@ -25,16 +26,17 @@
 //   * Blocks start where `out` is 128-byte aligned, so a block's stores cover
 //     whole lines whatever the alignment of the line.
 // Bound: HBM (or the last-level cache) for long lines, launch and one block's
-// latency for short ones.  Measured, a pass of 20 / 50 / 200 steps: 2^19 cells
-// 7.8 / 8.0 / 9.8 us, 2^22 11.7 / 11.9 / 15.5 us, 2^24 28 / 30 / 38 us, 2^26
-// 98 / 109 / 135 us (5.5 / 4.9 / 4.0 TB/s); the direct form needs 110 us for
-// 200 steps of 12345679 cells, this one 31 us.  At most 85 VGPRs (6 waves per
-// SIMD; the stepping path spills 47, which the others do not touch): with 128
-// (4 waves) 2^24 cells took 33.5 us in place of 30.
+// latency for short ones.  Measured, a pass of 20 / 50 / 200 steps: 2^20 cells
+// 5.3 / 5.6 / 6.5 us, 2^22 9.1 / 9.7 / 10.7 us, 2^24 26 / 27 / 33 us, 2^26
+// 98 / 104 / 134 us (5.5 / 5.2 / 4.0 TB/s); the direct form needs 110 us for
+// 200 steps of 12345679 cells, this one 26 us.  At most 85 VGPRs (6 waves per
+// SIMD; the stepping path spills 44, which the others do not touch): with 128
+// (4 waves) 2^24 cells and 50 steps took 12 % longer.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <limits>
 
 #include "hx_internal.h"
@@ -51,7 +53,6 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int kPlane = 36 * 64;   // bytes of one fp16 plane of the 1152-cell window
-constexpr int kTapHalf = 192;     // split taps of one level sent with a launch
 constexpr int kReach = 256;       // deepest pass
 // The shallowest pass the library takes in this form.  From here on its error
 // against 64 bits is the smaller one on positive noise and on smooth fields at
@@ -91,7 +92,9 @@ __device__ __forceinline__ float wave_max(float x) {
     return x;
 }
 
-// One partition as a block sees it.
+typedef __attribute__((address_space(1))) const float GF;
+
+// One run of cells as a block sees it: a partition or a segment.
 struct Part {
     const float* in;
     float* out;
@@ -101,24 +104,62 @@ struct Part {
     int hw;
 };
 
-// Cell c of the line: the partition's own, its neighbours' (clamped to what
-// they hold: cells further out meet no tap and no check), or the reflection.
+// Cell c of the line: the run's own, its neighbours' or the reflection.  Cells
+// further out than D meet no tap and no check; their index is clamped to what
+// is there.
 __device__ __forceinline__ float line_cell(const Part& s, int64_t c) {
-    if (c >= 0 && c < s.n) return s.in[c];
+    if (c >= 0 && c < s.n) return ((GF*)s.in)[c];
     if (c < 0) {
-        if (s.lo) return s.lo[s.hw + c < 0 ? 0 : s.hw + c];
-        return c == -1 ? 0.f : -s.in[-c - 2];
+        if (s.lo) return ((GF*)s.lo)[s.hw + c < 0 ? 0 : s.hw + c];
+        return c == -1 ? 0.f : -((GF*)s.in)[-c - 2 < s.n ? -c - 2 : s.n - 1];
     }
     const int64_t k = c - s.n;
-    if (s.hi) return s.hi[k >= s.hw ? s.hw - 1 : k];
-    return k == 0 ? 0.f : -s.in[s.n - k];
+    if (s.hi) return ((GF*)s.hi)[k >= s.hw ? s.hw - 1 : k];
+    return k == 0 ? 0.f : -((GF*)s.in)[k <= s.n ? s.n - k : 0];
 }
 
+// Cells c .. c + 3.  Four cells on one side of both ends are one load (of the
+// reflection, reversed); only a group that straddles an end takes its cells
+// one by one (each a round trip to memory: with all groups of an end's block
+// taken so, a batch of 4096 short segments ran at half speed).
 __device__ __forceinline__ f32x4 line_cells4(const Part& s, int64_t c, bool inside) {
-    if (inside) return *(__attribute__((address_space(1))) const f32x4u*)(s.in + c);
-    f32x4 v;
+    typedef __attribute__((address_space(1))) const f32x4u G;
+    if (inside) return *(G*)(s.in + c);
+    const float* base = s.in;
+    int64_t at = c;
+    bool whole = true, flip = false;
+    if (c + 4 <= 0) {
+        if (s.lo) {
+            base = s.lo;
+            at = s.hw + c < 0 ? 0 : s.hw + c;
+            whole = s.hw >= 4;
+        } else {
+            flip = true;
+            at = -c - 5 < s.n - 4 ? -c - 5 : s.n - 4;
+            whole = c < -4;
+        }
+    } else if (c >= s.n) {
+        const int64_t k = c - s.n;
+        if (s.hi) {
+            base = s.hi;
+            at = k < s.hw - 4 ? k : s.hw - 4;
+            whole = s.hw >= 4;
+        } else {
+            flip = true;
+            at = s.n - 3 - k > 0 ? s.n - 3 - k : 0;
+            whole = k > 0;
+        }
+    } else {
+        whole = c >= 0 && c + 4 <= s.n;
+    }
+    f32x4 v = {};
+    if (whole) {
+        v = *(G*)(base + at);
+        if (flip) v = f32x4{-v[3], -v[2], -v[1], -v[0]};
+    } else {
 #pragma unroll 1
-    for (int e = 0; e < 4; ++e) v[e] = line_cell(s, c + e);
+        for (int e = 0; e < 4; ++e) v[e] = line_cell(s, c + e);
+    }
     return v;
 }
 
@@ -132,23 +173,24 @@ __device__ __forceinline__ float far4(const f32x4& x) {
 // The stepping path of one block: its cells c0 .. c0 + 1023 advanced D steps
 // over the window of 256 cells on each side, 24 consecutive cells per lane, in
 // the rescaled direct form.
-__device__ __forceinline__ void step_line(const Part& s, const Seg1D& rate, int64_t c0, int D) {
+__device__ __forceinline__ void step_line(const Part& s, const PropLine& pl, int64_t c0) {
     constexpr int K = 24;
     const int l = threadIdx.x & 63;
     const int64_t b = c0 - kReach + (int64_t)K * l;
     float a[K];
 #pragma unroll
     for (int t = 0; t < K; ++t) a[t] = line_cell(s, b + t);
-    const float beta = (float)rate.beta, ap = (float)rate.alpha_p;
+    const float beta = pl.beta, ap = pl.ap;
+    const int D = pl.D, period = pl.period;
     int since = 0;
     for (int k = 0; k < D; ++k) {
         step_tile_scaled<float, K>(a, beta, false, false, 0, 0);
-        if (++since == rate.period) {
+        if (++since == period) {
             since = 0;
             scale_tile<float, K>(a, ap);
         }
     }
-    if (since) scale_tile<float, K>(a, (float)rate.alpha_rem);
+    if (since) scale_tile<float, K>(a, pl.ar);
 #pragma unroll
     for (int t = 0; t < K; ++t) {
         const int64_t c = b + t;
@@ -156,41 +198,20 @@ __device__ __forceinline__ void step_line(const Part& s, const Seg1D& rate, int6
     }
 }
 
-// What a launch needs besides the partitions.
-struct LineTaps {
-    uint16_t tap[2][kTapHalf];  // level (hi, lo) of tap j = -H - 31 + k, scaled by 2^texp
-    uint32_t levels;            // products per window chunk, as prop1d_levels16
-    int32_t texp, H, D;
-    float chk;                  // 2^21 E 2^texp: the check's threshold per unit of |x| in reach
-    uint32_t first[kMaxParts + 1];  // workgroups before partition p
-    uint32_t per;                   // the most workgroups a partition has
-};
-
-// NT: nontemporal loads of the block's own cells and stores (arrays that do
-// not stay in the caches between passes).
+// The blocks 4 wg .. 4 wg + 3 of one run, a wave each.  NT: nontemporal loads
+// of the block's own cells and stores (arrays that do not stay in the caches
+// between passes).
 template <int NC, bool NT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8)))
-void k_prop1d_line(PartSet1D ps, LineTaps a, Seg1D rate) {
+__device__ __forceinline__ void line_blocks(const Part& s, const PropLine& a, uint32_t wg,
+                                            char* lds_all, float* wmax) {
     constexpr int U = units_of(NC);
     constexpr int kUnits = 16 * U;
-    __shared__ __attribute__((aligned(16))) char lds_all[4 * 2 * kPlane + 16 * kUnits];
-    __shared__ float wmax[4];
     char* const tl = lds_all + 4 * 2 * kPlane;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     char* const lds = lds_all + wv * 2 * kPlane;
     const int l = threadIdx.x & 63, i = l & 31, g = l >> 5;
-    int p = (int)(blockIdx.x / a.per);
-    while (blockIdx.x >= a.first[p + 1]) ++p;
-    Part s;
-    s.in = static_cast<const float*>(ps.in[p]);
-    s.out = static_cast<float*>(ps.out[p]);
-    s.n = ps.n[p];
-    s.hw = a.D;
-    s.lo = p > 0 ? static_cast<const float*>(ps.in[p - 1]) + (ps.n[p - 1] - a.D)
-                 : static_cast<const float*>(ps.halo_lo);
-    s.hi = static_cast<const float*>(p + 1 < ps.count ? ps.in[p + 1] : ps.halo_hi);
     const int shift = (int)((reinterpret_cast<uintptr_t>(s.out) >> 2) & 31);
-    const int64_t c0 = 1024 * (4 * (int64_t)(blockIdx.x - a.first[p]) + wv) - shift;
+    const int64_t c0 = 1024 * (4 * (int64_t)wg + wv) - shift;
     const bool live = c0 < s.n;
     const bool inside = c0 >= kEdge && c0 + 1024 + kEdge <= s.n;
     // the window, as in the block walk: cells 256 j + 4 l of the block and 64
@@ -336,7 +357,7 @@ void k_prop1d_line(PartSet1D ps, LineTaps a, Seg1D rate) {
             fail = __ballot(!(mn >= thr)) != 0;
         }
         if (fail) {
-            step_line(s, rate, c0, a.D);
+            step_line(s, a, c0);
             return;
         }
     }
@@ -373,6 +394,63 @@ void k_prop1d_line(PartSet1D ps, LineTaps a, Seg1D rate) {
                 if (c >= 0 && c < s.n) s.out[c] = o[j][e];
             }
     }
+}
+
+// The workgroup's place in the line: workgroups go round the 8 XCDs in turn;
+// in each 128 of them an XCD takes 16 consecutive ones, whose edges (and, in a
+// batch, taps) then meet in its L2.  2^24 cells, 50 / 200 steps: 27.3 / 32.8 us
+// against 27.5 / 34.5 in launch order; 622 million cells, 20 steps: 833
+// against 858 (runs of 4: 889, of 64: 846, of 1024: 862).
+__device__ __forceinline__ uint32_t local_group() {
+    constexpr uint32_t C = 16, G = 8 * C;
+    const uint32_t b = blockIdx.x, k = b % G;
+    return b - k + G <= gridDim.x ? b - k + (k % 8) * C + k / 8 : b;
+}
+
+template <int NC>
+constexpr int kLineLds = 4 * 2 * kPlane + 16 * 16 * units_of(NC);
+
+// Neighbouring partitions: workgroups before partition p, and the most that a
+// partition has.
+struct LineGrid {
+    uint32_t first[kMaxParts + 1];
+    uint32_t per;
+};
+
+template <int NC, bool NT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8)))
+void k_prop1d_line(PartSet1D ps, PropLine a, LineGrid f) {
+    __shared__ __attribute__((aligned(16))) char lds[kLineLds<NC>];
+    __shared__ float wmax[4];
+    const uint32_t w = local_group();
+    int p = (int)(w / f.per);
+    while (w >= f.first[p + 1]) ++p;
+    Part s;
+    s.in = static_cast<const float*>(ps.in[p]);
+    s.out = static_cast<float*>(ps.out[p]);
+    s.n = ps.n[p];
+    s.hw = a.D;
+    s.lo = p > 0 ? static_cast<const float*>(ps.in[p - 1]) + (ps.n[p - 1] - a.D)
+                 : static_cast<const float*>(ps.halo_lo);
+    s.hi = static_cast<const float*>(p + 1 < ps.count ? ps.in[p + 1] : ps.halo_hi);
+    line_blocks<NC, NT>(s, a, w - f.first[p], lds, wmax);
+}
+
+template <int NC, bool NT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8)))
+void k_prop1d_segs(const LineSeg* __restrict__ segs, const uint32_t* __restrict__ wg_seg) {
+    __shared__ __attribute__((aligned(16))) char lds[kLineLds<NC>];
+    __shared__ float wmax[4];
+    const uint32_t w = local_group();
+    const LineSeg& q = segs[__builtin_amdgcn_readfirstlane(wg_seg[w])];
+    Part s;
+    s.in = q.in;
+    s.out = q.out;
+    s.n = q.n;
+    s.lo = q.lo;
+    s.hi = q.hi;
+    s.hw = q.hw;
+    line_blocks<NC, NT>(s, q.pl, w - q.first, lds, wmax);
 }
 
 // From this many cells on, a pass's arrays (8 bytes per cell) outgrow the
@@ -417,7 +495,7 @@ float to_half(float x, uint16_t* h) {
 
 }  // namespace
 
-bool propline_setup(double r, int D, PropLine* out) {
+bool propline_setup(double r, int D, PropLine* out, int min_H) {
     // (up to r = 1/4 the taps fall monotonically from p_0)
     if (!(r >= 1e-3 && r <= 0.25) || D < 1 || D > kReach) return false;
     std::vector<double> p;
@@ -431,7 +509,7 @@ bool propline_setup(double r, int D, PropLine* out) {
     std::vector<double> tail(K + 2, 0.0);  // tail[j] = sum of p_k, k >= j
     for (int j = K; j >= 0; --j) tail[j] = tail[j + 1] + p[j];
     auto past = [&](int j) { return j <= K ? tail[std::max(j, 0)] : 0.0; };
-    int H = 8;
+    int H = std::max(8, min_H);
     while (H < 64 && 2.0 * past(H + 1) > 1.8e-12) H += 8;
     const int NC = (32 + 2 * H) / 16;
     // products per chunk (prop1d_levels16's rule at 2^-40)
@@ -471,7 +549,7 @@ bool propline_setup(double r, int D, PropLine* out) {
     out->levels = levels;
     out->texp = texp;
     out->chk = (float)std::ldexp(E, 21 + texp);
-    std::fill(&out->tap[0][0], &out->tap[0][0] + 2 * kTapHalf, (uint16_t)0);
+    std::memset(out->tap, 0, sizeof out->tap);
     // (a tap's rounding is handed on to the next one out, whose lower half is
     // finer, so that the rounded taps still sum to 1: a smooth field meets the
     // sum of the roundings)
@@ -488,67 +566,79 @@ bool propline_setup(double r, int D, PropLine* out) {
             out->tap[1][k] = lo;
         }
     }
+    Seg1D rate{};
+    rate.r = r;
+    set_rate_1d(rate, D);
+    out->beta = (float)rate.beta;
+    out->ap = (float)rate.alpha_p;
+    out->ar = (float)rate.alpha_rem;
+    out->period = rate.period;
     return true;
 }
 
-// Fitted to passes of 20 to 200 steps over lines from 2^12 to 2^28 cells
-// (deviation at most 9 %).
-double propline_us(double r, int64_t cells, int D) {
+// Fitted to passes of 20 to 200 steps over lines from 2^18 to 2^28 cells
+// (deviation at most 6 %).
+double propline_us(double r, int64_t cells, int D, bool setup) {
     const double v = 2.0 * r * D;
     if (!(r >= 1e-3 && r <= 0.25) || D < kPropMinDepth || D > kReach || v > 104.0 ||
         cells < kPropLineMin)
         return std::numeric_limits<double>::infinity();
     const int H = std::min(64, ((int)(7.05 * std::sqrt(v)) + 8) / 8 * 8), NC = 2 + H / 8;
-    const double setup = 0.5 + std::min(4.5, 0.028 * D);
-    return setup + 6.4 + 0.16 * NC + (D > 64 ? 1.2 : 0.0) +
-           1e-6 * (double)cells * (1.19 + 0.03 * NC + (D > 64 ? 0.3 : 0.0));
+    const double m = 1e-6 * (double)cells;
+    return (setup ? 0.5 + std::min(4.5, 0.028 * D) : 0.0) + 5.2 + 0.1 * NC +
+           (D > 64 ? 0.4 : 0.0) + (0.75 + 0.02 * NC) * std::min(m, 4.0) +
+           (1.13 + 0.04 * NC + (D > 64 ? 0.34 : 0.0)) * std::max(0.0, m - 4.0);
 }
 
+#define HX_LINE_SWITCH(H, nt, ...)  \
+    switch ((32 + 2 * (H)) / 16) {  \
+        HX_LINE_CASE(3, nt, __VA_ARGS__)  \
+        HX_LINE_CASE(4, nt, __VA_ARGS__)  \
+        HX_LINE_CASE(5, nt, __VA_ARGS__)  \
+        HX_LINE_CASE(6, nt, __VA_ARGS__)  \
+        HX_LINE_CASE(7, nt, __VA_ARGS__)  \
+        HX_LINE_CASE(8, nt, __VA_ARGS__)  \
+        HX_LINE_CASE(9, nt, __VA_ARGS__)  \
+        HX_LINE_CASE(10, nt, __VA_ARGS__) \
+    default: return hipErrorInvalidValue; \
+    }
+
 hipError_t launch_propline(const PartSet1D& set, const PropLine& pl, hipStream_t stream) {
-    static_assert(sizeof(PropLine::tap) == sizeof(LineTaps::tap), "one table");
     if (set.count < 1 || set.count > kMaxParts) return hipErrorInvalidValue;
-    LineTaps a{};
-    std::copy(&pl.tap[0][0], &pl.tap[0][0] + 2 * kTapHalf, &a.tap[0][0]);
-    a.levels = pl.levels;
-    a.texp = pl.texp;
-    a.H = pl.H;
-    a.D = pl.D;
-    a.chk = pl.chk;
+    LineGrid f{};
     int64_t cells = 0;
     for (int p = 0; p < set.count; ++p) {
         if (set.n[p] < kPropLineMin) return hipErrorInvalidValue;
-        const int shift = (int)((reinterpret_cast<uintptr_t>(set.out[p]) >> 2) & 31);
-        const int64_t wg = (set.n[p] + shift + 4095) / 4096;
-        if (a.first[p] + wg >= (int64_t(1) << 31)) return hipErrorInvalidValue;
-        a.first[p + 1] = a.first[p] + (uint32_t)wg;
-        a.per = std::max(a.per, (uint32_t)wg);
+        const int64_t wg = propline_wgs(set.out[p], set.n[p]);
+        if (f.first[p] + wg >= (int64_t(1) << 24)) return hipErrorInvalidValue;
+        f.first[p + 1] = f.first[p] + (uint32_t)wg;
+        f.per = std::max(f.per, (uint32_t)wg);
         cells += set.n[p];
     }
-    Seg1D rate{};
-    rate.r = set.r;
-    set_rate_1d(rate, pl.D);
-    const dim3 grid(a.first[set.count]), block(256);
-    const bool nt = cells >= kNtCells;
-    switch ((32 + 2 * pl.H) / 16) {
-#define HX_LINE_CASE(N)                                                                        \
-    case N:                                                                                    \
-        if (nt)                                                                                \
-            hipLaunchKernelGGL((k_prop1d_line<N, true>), grid, block, 0, stream, set, a, rate); \
-        else                                                                                   \
-            hipLaunchKernelGGL((k_prop1d_line<N, false>), grid, block, 0, stream, set, a, rate); \
+    const dim3 grid(f.first[set.count]), block(256);
+#define HX_LINE_CASE(N, nt, ...)                                                              \
+    case N:                                                                                   \
+        if (nt) hipLaunchKernelGGL((k_prop1d_line<N, true>), grid, block, 0, stream, __VA_ARGS__); \
+        else hipLaunchKernelGGL((k_prop1d_line<N, false>), grid, block, 0, stream, __VA_ARGS__);   \
         break;
-        HX_LINE_CASE(3)
-        HX_LINE_CASE(4)
-        HX_LINE_CASE(5)
-        HX_LINE_CASE(6)
-        HX_LINE_CASE(7)
-        HX_LINE_CASE(8)
-        HX_LINE_CASE(9)
-        HX_LINE_CASE(10)
+    HX_LINE_SWITCH(pl.H, cells >= kNtCells, set, pl, f)
 #undef HX_LINE_CASE
-    default: return hipErrorInvalidValue;
-    }
     return hipGetLastError();
 }
+
+hipError_t launch_propline_batch(const LineSeg* segs_dev, const uint32_t* wg_seg_dev, int64_t nwg,
+                                 int64_t cells, int H, hipStream_t stream) {
+    if (nwg < 1 || nwg >= (int64_t(1) << 24)) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)nwg), block(256);
+#define HX_LINE_CASE(N, nt, ...)                                                              \
+    case N:                                                                                   \
+        if (nt) hipLaunchKernelGGL((k_prop1d_segs<N, true>), grid, block, 0, stream, __VA_ARGS__); \
+        else hipLaunchKernelGGL((k_prop1d_segs<N, false>), grid, block, 0, stream, __VA_ARGS__);   \
+        break;
+    HX_LINE_SWITCH(H, cells >= kNtCells, segs_dev, wg_seg_dev)
+#undef HX_LINE_CASE
+    return hipGetLastError();
+}
+#undef HX_LINE_SWITCH
 
 }  // namespace hx

@@ -139,7 +139,7 @@ static hx_status launch_1d(Ctx* c, const hx_stencil_args* a, const hx_event* dep
     for (int d : plan) {
         Pass1D ps{};
         if (choose && d <= max_time_block_1d(dt, 16)) {
-            ps = choose_pass1d(dt, a->r, &n, 1, d);
+            ps = choose_pass1d(dt, a->r, &n, 1, d, ghost);
             ps.prop = ps.prop && cell_aligned;
         } else {
             ps.g = g;

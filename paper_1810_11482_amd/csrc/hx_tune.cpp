@@ -369,6 +369,21 @@ extern "C" hx_status hx_tune_batched(hx_ctx ctx, const hx_batch_desc* desc, int 
     g.grid = best->grid_waves_per_cu;
     g.mode = 1 + best->form;
     g.rows = best->form == HX_FORM_PROPAGATOR ? best->span_blocks : 0;
+    // *best is the fastest plan that can be named; an AUTO plan that names
+    // nothing keeps the library's own choice if that is faster still
+    if (best->steps == T && desc->dtype == HX_F32) {
+        const TuneKey k = tune_key_batched(desc->dtype, total, desc->count, T);
+        tune_erase(k);
+        hx_batch_desc own = *desc;
+        own.form = HX_FORM_AUTO;
+        own.cells_per_lane = own.waves_per_group = own.grid_waves_per_cu = own.span_blocks = 0;
+        hx_plan plan = 0;
+        if (hx_plan_create_batched(ctx, &own, &plan) == HX_OK) {
+            const double t_own = time_plan(ctx, plan, 3);
+            hx_plan_destroy(ctx, plan);
+            if (t_own > 0 && t_own < best_t) g.mode = 1 + HX_FORM_AUTO;
+        }
+    }
     // under the run's key (its depth is the answer) and the pass's key (a plan
     // made for one pass of that depth finds its geometry)
     tune_store(tune_key_batched(desc->dtype, total, desc->count, T), g);

@@ -20,7 +20,8 @@ struct TunedGeom {
     int wpg = 0;       // waves per group
     int rows = 0;      // 2D rows per wave
     int grid = 0;      // batched: waves per CU
-    int mode = 0;      // batched: chosen hx_batch_form + 1 (0 = none)
+    int mode = 0;      // batched: chosen hx_batch_form + 1 (0 = none; AUTO: a plan that
+                       // names nothing is faster than every one that can be named)
                        // (a batched propagator keeps its span_blocks in `rows`);
                        // 1D/2D stencils: 1 = the library's own choice was faster
                        // than every geometry that can be named

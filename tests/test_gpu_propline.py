@@ -148,3 +148,53 @@ def test_partitions(ctx, periodic, sizes):
     check(got, u0, r, steps, PER if periodic else ZERO)
     f = oracle.heat1d_periodic if periodic else oracle.heat1d_dirichlet
     assert rel_l2(got, f(u0.astype(np.float64), r, steps)) <= 1e-5
+
+
+@pytest.mark.parametrize("steps,n0", [(20, 1 << 18), (50, 256), (64, 256), (100, 257), (200, 300)])
+def test_batch_of_any_segments(ctx, steps, n0):
+    """AUTO batches the walks do not take: sizes, rates, alignments and ends of
+    every kind in one launch, at the smallest segments it serves and up."""
+    sizes = [n0, n0 + 1, n0 + 3, 1023, 1024, 1025, 4095, 4096, 4097, 8191, 12347, 30001]
+    sizes = [max(m, n0) for m in sizes] * 2
+    g = np.random.default_rng(steps)
+    rates = g.uniform(0.05, 0.25, len(sizes))
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    u0 = field("signed", int(off[-1]), steps)
+    u0[off[3]:off[3] + 400] = 0
+    u0[off[3] + 200] = 1e10
+    u0[off[5] + 7] = np.inf
+    hw = steps + 5
+    halos = g.random((len(sizes), 2, hw)).astype(np.float32)
+    src, halo = upload(ctx, u0), upload(ctx, halos.ravel())
+    ends = [(PER, PER), (ZERO, ZERO), (GHOST, GHOST), (ZERO, GHOST), (GHOST, ZERO)]
+    outs = []
+    for kw in (dict(form=hx.HX_FORM_AUTO), dict(form=hx.HX_FORM_DIRECT)):
+        out = upload(ctx, np.full(u0.size + 64, 7.0, np.float32))
+        segs = [hx.segment(inp=src, in_offset=4 * int(off[k]), out=out, out_offset=4 * int(off[k]),
+                           n=m, r=float(rates[k]), bc_lo=ends[k % 5][0], bc_hi=ends[k % 5][1],
+                           halo_lo=halo, halo_lo_offset=8 * hw * k, halo_hi=halo,
+                           halo_hi_offset=8 * hw * k + 4 * hw, halo_width=hw)
+                for k, m in enumerate(sizes)]
+        plan = hx.hx_plan_create_batched(ctx, hx.HX_F32, steps, segs, **kw)
+        ev = hx.hx_launch_batched(ctx, plan)
+        assert hx.hx_wait(ctx, ev) == hx.HX_OK, hx.hx_last_error(ctx)
+        hx.hx_event_release(ctx, ev)
+        outs.append(download(ctx, out, u0.size + 64, np.float32))
+        hx.hx_plan_destroy(ctx, plan)
+        hx.hx_buffer_destroy(ctx, out)
+    assert np.all(outs[0][u0.size:] == 7.0)
+    assert not np.array_equal(outs[0], outs[1], equal_nan=True)  # this form, not the direct one
+    for k, m in enumerate(sizes):
+        u = u0[off[k]:off[k] + m].astype(np.float64)
+        lo, hi = ends[k % 5]
+        got = outs[0][off[k]:off[k] + m]
+        if lo == PER:
+            check(got, u, rates[k], steps, PER)
+            continue
+        # zero ends as the odd reflection, halos as they are
+        z = np.zeros(1)
+        left = halos[k, 0][-steps:] if lo == GHOST else np.concatenate([-u[::-1], z])[-steps:]
+        right = halos[k, 1][:steps] if hi == GHOST else np.concatenate([z, -u[::-1]])[:steps]
+        check(got, u, rates[k], steps, GHOST, (left, right))
+    for b in (src, halo):
+        hx.hx_buffer_destroy(ctx, b)
