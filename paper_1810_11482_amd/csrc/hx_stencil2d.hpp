@@ -153,9 +153,10 @@ struct FastIO {
                                         // RAG: of each vector's first cell)
 };
 
-// x where m is all ones, 0 where it is 0: one operation, and (unlike a select
-// on a condition per cell) nothing the compiler turns into branches around
-// each cell's step, which made a RAG edge row 1.5 times as slow.
+// x where m is all ones, 0 where it is 0: nothing (unlike a select on a
+// condition) the compiler turns into a branch around each cell's step or, for
+// a zero row, around its load and the wait for it, which made a RAG edge row
+// 1.5 times as slow and a whole 4096^2 pass in double by a fifth.
 __device__ __forceinline__ float keep(float x, uint32_t m) {
     return __uint_as_float(__float_as_uint(x) & m);
 }
@@ -183,6 +184,7 @@ __device__ __forceinline__ void load_fast(const FastIO<T, C>& io, int64_t y, T (
     constexpr int VN = V16<T>::N;
     y = y < io.ylo ? io.ylo : (y > io.yhi ? io.yhi : y);
     const bool zr = EDGE && zero_row_fast(io, y);
+    const uint32_t zm = zr ? 0u : ~0u;
     const int64_t ys = zr ? 0 : y;
     const bool lo = ys < 0, hi = ys >= io.ny;
     const int64_t row = lo ? io.hw + ys : (hi ? ys - io.ny : ys);
@@ -193,7 +195,7 @@ __device__ __forceinline__ void load_fast(const FastIO<T, C>& io, int64_t y, T (
 #pragma unroll
         for (int j = 0; j < C; ++j) {
             const T x = *(__attribute__((address_space(1))) const T*)(base + io.xload[j]);
-            dst[j] = keep(keep(x, io.col[j]), zr ? 0u : ~0u);
+            dst[j] = keep(x, io.col[j] & zm);
         }
     } else {
 #pragma unroll
@@ -202,7 +204,7 @@ __device__ __forceinline__ void load_fast(const FastIO<T, C>& io, int64_t y, T (
 #pragma unroll
             for (int e = 0; e < VN; ++e) {
                 const int j = q * VN + e;
-                dst[j] = !EDGE ? x[e] : (zr ? T(0) : keep(x[e], io.col[q * VN]));
+                dst[j] = EDGE ? keep(x[e], io.col[q * VN] & zm) : x[e];
             }
         }
     }
@@ -264,7 +266,7 @@ __device__ __forceinline__ void row_step_fast(const FastIO<T, C>& io, T*& orow, 
         const T left = dpp_move<DPP_WAVE_SHR1>(cn[C - 1]);
         const T right = dpp_move<DPP_WAVE_SHL1>(cn[0]);
         T* dst = l + 1 < D ? R[l + 1 < D ? l + 1 : 0][M3] : last;
-        const bool zr = EDGE && zero_row_fast(io, yy - l - 1);
+        const uint32_t zm = EDGE && zero_row_fast(io, yy - l - 1) ? 0u : ~0u;
 #pragma unroll
         for (int j = 0; j < C; ++j) {
             const T c = cn[j];
@@ -272,10 +274,7 @@ __device__ __forceinline__ void row_step_fast(const FastIO<T, C>& io, T*& orow, 
             const T ns = no[j] + so[j];
             const T t = ns + we;
             const T v = update<T, SC>(rt, c, t);
-            if constexpr (EDGE && RAG)
-                dst[j] = keep(keep(v, io.col[j]), zr ? 0u : ~0u);
-            else
-                dst[j] = !EDGE ? v : (zr ? T(0) : keep(v, io.col[j / VN * VN]));
+            dst[j] = EDGE ? keep(v, io.col[RAG ? j : j / VN * VN] & zm) : v;
         }
         rescale_level<T, C, D, SC>(rt, l, dst);
     }

@@ -386,12 +386,41 @@ double tile_us(const TileCost& c, int64_t tiles, int depth) {
     return c.a + std::max(depth * c.l, depth * g * c.i + g * c.m);
 }
 
-// From this many float cells on, the streaming form's smaller redundancy wins:
-// 10000 x 12000 cells 29.6 us per step against 31.1, 16384^2 55.6 against
-// 61.7, but 8192^2 20.0 against 18.0.  In double the tile form won at every
-// size measured (16384^2: 110 against 118 us).
+// From this many float cells on, the streaming form's smaller redundancy wins at
+// every depth: 10000 x 12000 cells 29.6 us per step against 31.1, 16384^2 55.6
+// against 61.7.
 constexpr double kStreamCells = 1.0e8;
+
 constexpr int kTileMax = 24;  // deepest tile pass considered
+
+// Below that, and in double, the streaming form takes passes of up to 8 steps
+// where it is modelled faster, with few rows per wave (16, 24 or 32: more waves
+// and shorter chains against up to a doubling of the work).  t = a + max(S (l0 +
+// D l), q (S m + (rows + D) D i), bytes) (1 + rag) + c min(the last two), with
+// S = rows + 2 D row steps, w the waves per SIMD and q w rounded up half way
+// while it is small, bytes = 2 per cell at bw (1 + h / w).  Fitted to passes of
+// 2 to 8 steps over 14 grids from 512^2 to 16384^2, aligned and ragged, whole
+// and in bands (mean deviation 7-8 %).  Measured, stream / tile: 4096^2 in 16
+// bands, 4 steps, 35 / 42 us float, 55 / 63 double; 9000 x 2300 in 23 bands, 6
+// steps, 54 / 69 and 99 / 127; 10001 x 10000, 8 steps, double 398 / 491;
+// 2048^2, 4 steps, 20.8 / 17.7; 8192^2, 4 steps, 127 / 119.
+struct StreamCost {
+    double a, l0, l, m, i, bw, rag, h, c;
+};
+constexpr StreamCost kStreamCost[2] = {
+    {6.70, 0.387, 0.0374, 0.0, 0.0419, 5.12e6, 0.0185, 0.648, 0.21},
+    {4.61, 0.421, 0.0411, 0.333, 0.0354, 4.49e6, 0.0426, 0.124, 0.054}};
+
+double stream_us(int dtype, int64_t nx, int64_t waves, double cells, int depth, int rows) {
+    const StreamCost& k = kStreamCost[dtype ? 1 : 0];
+    const double w = (double)waves / 1024.0, s = rows + 2 * depth;
+    const double q = w < 4.0 ? 0.5 * (w + std::ceil(w - 0.02)) : w + 0.3;
+    const double comp = q * (s * k.m + (rows + depth) * depth * k.i);
+    const double bytes = cells * (dtype ? 16 : 8) / k.bw * (1.0 + k.h / std::max(w, 0.1));
+    const double rag = nx % (dtype ? 2 : 4) ? k.rag : 0.0;
+    return k.a + std::max(std::max(s * (k.l0 + k.l * depth), comp), bytes) * (1.0 + rag) +
+           k.c * std::min(comp, bytes);
+}
 
 }  // namespace
 
@@ -406,9 +435,9 @@ Form2D choose_form2d(int dtype, int64_t nx, const int64_t* ny, int n, int depth,
         // 16384^2: 10 steps 556 us at 56 rows per wave and one wave per
         // workgroup (561 at 64 and four), 8 steps 496 us at 48 and four, 12
         // and 16 steps 754 and 1029 us at 96 and one; shallow passes are bound
-        // by their bytes
+        // by their bytes, and most waves fetch them fastest
         f.tile = false;
-        f.g.rows = depth <= 8 ? 48 : (depth == 10 ? 56 : 96);
+        f.g.rows = depth <= 6 ? 24 : (depth <= 8 ? 48 : (depth == 10 ? 56 : 96));
         f.g.wpg = depth <= 8 ? 4 : 1;
         const double step = depth <= 8 ? 2.30e-7 : (depth == 10 ? 2.08e-7 : 2.40e-7);
         *us = cells * std::max(depth * step, 1.6e-6);
@@ -422,11 +451,24 @@ Form2D choose_form2d(int dtype, int64_t nx, const int64_t* ny, int n, int depth,
         if (hout < 1) continue;
         int64_t tiles = 0;
         for (int k = 0; k < n; ++k) tiles += strips * ((ny[k] + hout - 1) / hout);
-        const double t = tile_us(c, tiles, depth);
+        // (in runs of passes the tile form takes 1.2 times the fitted time)
+        const double t = 1.2 * tile_us(c, tiles, depth);
         if (*us == 0.0 || t < *us) {
             *us = t;
             f.g.rows = c.rows;
             f.g.wpg = c.wpg;
+        }
+    }
+    for (int rows : {16, 24, 32}) {
+        if (depth < 1 || depth > 8 || !stencil2d_supported(dtype, 4, depth)) break;
+        int64_t waves = 0;
+        for (int k = 0; k < n; ++k) waves += strips * ((ny[k] + rows - 1) / rows);
+        const double t = stream_us(dtype, nx, waves, cells, depth, rows);
+        if (t < *us) {
+            *us = t;
+            f.tile = false;
+            f.g.rows = rows;
+            f.g.wpg = 4;
         }
     }
     return f;
