@@ -54,6 +54,13 @@ hx_status check_common(Ctx* c, int dtype, int64_t nx, int64_t ny) {
     return HX_OK;
 }
 
+hipError_t run_forward(int dt, const VCPass& p, const VCArgs& v, hipStream_t st, void* mid,
+                       int64_t stride) {
+    return p.waves ? launch_vc_tile(dt, false, p.steps, p.waves, v, mid, stride, nullptr, false,
+                                    nullptr, st)
+                   : launch_vc_forward(dt, p.steps, v, st, mid, stride);
+}
+
 }  // namespace
 
 #define LOCK_CTX(ctx)                                  \
@@ -133,11 +140,16 @@ hx_status hx_heat_vc_forward(hx_ctx ctx, const hx_vc_args* a, const hx_event* de
         return pw + (size_t)(t % 2) * bytes;
     };
     // Grids the fused kernels take run each stretch between kept states (u0,
-    // the checkpoints, uT) in fused passes of up to kVcFusedMax steps, as even
-    // as the stretch allows, ping-ponging through the two work states; the
-    // others step by step.  Both give the same bits.
+    // the checkpoints, uT) in fused passes (choose_vc_passes; streaming ones
+    // only where the rows per block are given), ping-ponging through the two
+    // work states; the others step by step.  All give the same bits.
     VCArgs probe{pu0, pk, nullptr, puT, nullptr, nx, ny, tau, rows};
     const bool fused = vc_fused_supported(dt, probe);
+    std::vector<VCPass> full, tail;  // of a whole stretch, and of the last one
+    if (fused) {
+        full = choose_vc_passes(dt, 0, nx, ny, S, rows <= 0);
+        tail = choose_vc_passes(dt, 0, nx, ny, T - (sc.nseg - 1) * S, rows <= 0);
+    }
     return c->submit(SC_COMPUTE, deps, ndeps, acc, "heat_vc_forward",
                      [=](hipStream_t st) -> hipError_t {
                          if (T == 0)
@@ -152,15 +164,14 @@ hx_status hx_heat_vc_forward(hx_ctx ctx, const hx_vc_args* a, const hx_event* de
                              return hipSuccess;
                          }
                          for (int t0 = 0; t0 < T; t0 += S) {
-                             const int t1 = std::min(t0 + S, T);
-                             const int L = t1 - t0;
-                             const int np = (L + kVcFusedMax - 1) / kVcFusedMax;
+                             const std::vector<VCPass>& ps = t0 + S < T ? full : tail;
+                             const int np = (int)ps.size();
                              char* src = loc(t0);
                              for (int j = 0; j < np; ++j) {
-                                 const int d = L / np + (j < L % np ? 1 : 0);
-                                 char* dst = j + 1 == np ? loc(t1) : pw + (size_t)(j % 2) * bytes;
+                                 char* dst = j + 1 == np ? loc(std::min(t0 + S, T))
+                                                         : pw + (size_t)(j % 2) * bytes;
                                  VCArgs v{src, pk, nullptr, dst, nullptr, nx, ny, tau, rows};
-                                 hipError_t e = launch_vc_forward(dt, d, v, st);
+                                 hipError_t e = run_forward(dt, ps[j], v, st, nullptr, 0);
                                  if (e != hipSuccess) return e;
                                  src = dst;
                              }
@@ -205,11 +216,18 @@ hx_status hx_heat_vc_backward(hx_ctx ctx, const hx_vc_args* a, const hx_event* d
     // Grids the fused kernels take recompute each segment's states in fused
     // passes that store every level (one read of the state and of kappa per
     // pass instead of per step), and run the reverse sweep in fused passes of
-    // up to four adjoint steps with their gradient terms (lam moving between
-    // the two work slots, the last pass into lam0); the others step by step.
-    // Both give the same bits.
+    // adjoint steps with their gradient terms (lam moving between the two work
+    // slots, the last pass into lam0); the others step by step.  Streaming
+    // adjoint passes of doubles take at most two steps: deeper ones need more
+    // than the 512 registers a wave can hold.  All give the same bits.
     VCArgs probe{pu0, pk, nullptr, pseg ? pseg : pu0, nullptr, nx, ny, tau, rows};
     const bool fused = vc_fused_supported(dt, probe);
+    std::vector<VCPass> re[2], adj[2];  // recompute and sweep of a whole segment, of the last
+    for (int q = 0; fused && q < 2; ++q) {
+        const int L = q ? T - (nseg - 1) * S : S;
+        re[q] = choose_vc_passes(dt, 1, nx, ny, L - 1, rows <= 0);
+        adj[q] = choose_vc_passes(dt, 2, nx, ny, L, rows <= 0);
+    }
     return c->submit(
         SC_COMPUTE, deps, ndeps, acc, "heat_vc_backward",
         [=](hipStream_t st) -> hipError_t {
@@ -225,20 +243,20 @@ hx_status hx_heat_vc_backward(hx_ctx ctx, const hx_vc_args* a, const hx_event* d
                 auto ut = [=](int t) -> const char* {
                     return t == t0 ? uck : pseg + (size_t)(t - t0 - 1) * bytes;
                 };
-                if (fused && t1 - t0 > 1) {  // recompute the segment, fused
-                    const int nst = t1 - t0 - 1;  // states t0+1 .. t1-1, slots 0 .. nst-1
-                    const int np = (nst + kVcFusedMax - 1) / kVcFusedMax;
+                const int last = k == nseg - 1 ? 1 : 0;
+                if (fused) {  // recompute the segment, fused
+                    // states t0+1 .. t1-1 into slots 0 ..
                     const char* src = uck;
-                    for (int j = 0, done = 0; j < np; ++j) {
-                        const int d = nst / np + (j < nst % np ? 1 : 0);
+                    int done = 0;
+                    for (const VCPass& p : re[last]) {
                         char* mid = pseg + (size_t)done * bytes;
-                        char* dst = pseg + (size_t)(done + d - 1) * bytes;
+                        char* dst = pseg + (size_t)(done + p.steps - 1) * bytes;
                         VCArgs v{src, pk, nullptr, dst, nullptr, nx, ny, tau, rows};
-                        if ((e = launch_vc_forward(dt, d, v, st, d > 1 ? mid : nullptr,
-                                                   (int64_t)bytes)) != hipSuccess)
+                        if ((e = run_forward(dt, p, v, st, p.steps > 1 ? mid : nullptr,
+                                             (int64_t)bytes)) != hipSuccess)
                             return e;
                         src = dst;
-                        done += d;
+                        done += p.steps;
                     }
                 } else {
                     for (int t = t0 + 1; t < t1; ++t) {  // recompute the segment
@@ -248,28 +266,23 @@ hx_status hx_heat_vc_backward(hx_ctx ctx, const hx_vc_args* a, const hx_event* d
                     }
                 }
                 if (fused) {  // reverse sweep, fused
-                    // at most two steps per FP64 pass: deeper FP64 passes need
-                    // more than the 512 registers a wave can hold and spill
-                    // hundreds of them to scratch (any depth gives the same bits)
-                    const int L = t1 - t0;
-                    const int dmax = dt == HX_F32 ? kVcFusedMax : 2;
-                    const int np = (L + dmax - 1) / dmax;
+                    const int np = (int)adj[last].size();
                     int tb = t1 - 1;
                     for (int j = 0; j < np; ++j) {
-                        const int d = L / np + (j < L % np ? 1 : 0);
-                        const void* us[kVcFusedMax] = {};
-                        for (int q = 0; q < d; ++q) us[q] = ut(tb - q);
-                        char* dst = tb - d + 1 == 0 ? pl0 : (cur == pw ? pw + bytes : pw);
+                        const VCPass& p = adj[last][j];
+                        const void* us[kVcTileMax] = {};
+                        for (int q = 0; q < p.steps; ++q) us[q] = ut(tb - q);
+                        char* dst = tb - p.steps + 1 == 0 ? pl0 : (cur == pw ? pw + bytes : pw);
                         VCArgs v{nullptr, pk, cur, dst, pga, nx, ny, tau, rows};
                         // the first pass starts the segment's accumulator at
                         // zero, the last folds it into the FP64 total
-                        if ((e = launch_vc_adjoint(
-                                 dt, d, v, us, st, j == 0,
-                                 j + 1 == np ? reinterpret_cast<double*>(pg64) : nullptr)) !=
-                            hipSuccess)
-                            return e;
+                        double* total = j + 1 == np ? reinterpret_cast<double*>(pg64) : nullptr;
+                        e = p.waves ? launch_vc_tile(dt, true, p.steps, p.waves, v, nullptr, 0, us,
+                                                     j == 0, total, st)
+                                    : launch_vc_adjoint(dt, p.steps, v, us, st, j == 0, total);
+                        if (e != hipSuccess) return e;
                         cur = dst;
-                        tb -= d;
+                        tb -= p.steps;
                     }
                     continue;  // folded
                 } else {

@@ -462,6 +462,22 @@ hipError_t launch_vc_step(int dtype, bool adjoint, const VCArgs& v, hipStream_t 
 // that many single steps); for grids with nx >= 4 and under 2 GiB
 // (vc_fused_supported), else hipErrorInvalidValue.
 constexpr int kVcFusedMax = 4;
+// The tile form of a pass of up to kVcTileMax steps (hx_vctile.hip; `waves`
+// waves per workgroup: 2 to 16 forward in float, else 2 to 8; 2 steps < 4
+// waves), any grid: forward with mid as launch_vc_forward, adjoint as
+// launch_vc_adjoint.  The same bits.
+constexpr int kVcTileMax = 12;
+hipError_t launch_vc_tile(int dtype, bool adjoint, int steps, int waves, const VCArgs& v,
+                          void* mid, int64_t mid_stride, const void* const* ustates, bool zin,
+                          double* total, hipStream_t stream);
+// The passes of a stretch of `steps` steps (kind 0: forward, 1: forward storing
+// every state, 2: adjoint), by modelled time: `waves` of the tile form, or 0:
+// the streaming form.  tiles false: streaming passes only.
+struct VCPass {
+    int steps, waves;
+};
+std::vector<VCPass> choose_vc_passes(int dtype, int kind, int64_t nx, int64_t ny, int steps,
+                                     bool tiles);
 bool vc_fused_supported(int dtype, const VCArgs& v);
 // mid (stride of at least one state): also store the states after steps 1 .. steps-1 at mid + (k-1) * mid_stride.
 hipError_t launch_vc_forward(int dtype, int steps, const VCArgs& v, hipStream_t stream,
