@@ -642,10 +642,15 @@ Pass1D choose_pass1d(int dtype, double r, const int64_t* n, int count, int depth
         cells += n[k];
         least = std::min(least, n[k]);
     }
-    // (a partition node of under 4096 cells gains 1 us of 9 at most up to 64
-    // steps; in the direct form its bits are the whole pass's over its array)
-    const int64_t min_n = fed && depth <= 64 ? 4096 : kPropLineMin;
-    if (dtype == 0 && least >= min_n && propline_us(r, cells, depth) < us)
+    // (a node of a graph of partitions costs the host about 11 us; up to 64
+    // steps the taps and the larger kernel argument add to that what the kernel
+    // saves unless the node is long: 16 nodes of 2^20 cells, 50 steps, between
+    // their copies: 2.31 ms against 2.24.  Below 4096 cells the node's bits
+    // stay those of the whole pass over its array, too)
+    const bool node = fed && depth <= 64;
+    const int64_t min_n = node ? 4096 : kPropLineMin;
+    const double host_us = node && count == 1 ? 8.0 : 0.0;
+    if (dtype == 0 && least >= min_n && propline_us(r, cells, depth) + host_us < us)
         p.prop = propline_setup(r, depth, &p.pl);
     return p;
 }

@@ -164,6 +164,12 @@ __device__ __forceinline__ double keep(double x, uint32_t m) {
     return __hiloint2double(__double2hiint(x) & (int)m, __double2loint(x) & (int)m);
 }
 
+// Where the branches are cheaper all the same: the straight-line edge code of
+// eight float levels needs 137 registers, three waves per SIMD in place of four
+// for the interior waves, too (16384^2 at 32 rows per wave: 512 us against 474).
+template <typename T, int C, int D, bool RAG>
+constexpr bool kEdgeBranch = sizeof(T) == 4 && C == 4 && D == 8 && !RAG;
+
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 constexpr int BUF_DWORD3 = 0x00020000;  // raw 32-bit buffer (gfx9 family)
@@ -177,7 +183,7 @@ __device__ __forceinline__ bool zero_row_fast(const FastIO<T, C>& io, int64_t y)
            (y >= io.ny && (!io.bot_ghost || y >= io.ny + io.hw));
 }
 
-template <typename T, int C, bool EDGE, bool RAG>
+template <typename T, int C, int D, bool EDGE, bool RAG>
 __device__ __forceinline__ void load_fast(const FastIO<T, C>& io, int64_t y, T (&dst)[C]) {
     typedef typename V16<T>::u UT;
     typedef __attribute__((address_space(1))) const char GC;
@@ -204,7 +210,10 @@ __device__ __forceinline__ void load_fast(const FastIO<T, C>& io, int64_t y, T (
 #pragma unroll
             for (int e = 0; e < VN; ++e) {
                 const int j = q * VN + e;
-                dst[j] = EDGE ? keep(x[e], io.col[q * VN] & zm) : x[e];
+                if constexpr (EDGE && kEdgeBranch<T, C, D, RAG>)
+                    dst[j] = zr ? T(0) : keep(x[e], io.col[q * VN]);
+                else
+                    dst[j] = EDGE ? keep(x[e], io.col[q * VN] & zm) : x[e];
             }
         }
     }
@@ -256,7 +265,7 @@ __device__ __forceinline__ void row_step_fast(const FastIO<T, C>& io, T*& orow, 
                                               const Rate2<T>& rt) {
     constexpr int VN = V16<T>::N;
     constexpr int M3 = M % 3, OLD = (M3 + 1) % 3, NEW = (M3 + 2) % 3;
-    load_fast<T, C, EDGE, RAG>(io, yy + Q - 3, Z[(M + Q - 3) % Q]);
+    load_fast<T, C, D, EDGE, RAG>(io, yy + Q - 3, Z[(M + Q - 3) % Q]);
     T last[C];
 #pragma unroll
     for (int l = 0; l < LV; ++l) {
@@ -266,7 +275,8 @@ __device__ __forceinline__ void row_step_fast(const FastIO<T, C>& io, T*& orow, 
         const T left = dpp_move<DPP_WAVE_SHR1>(cn[C - 1]);
         const T right = dpp_move<DPP_WAVE_SHL1>(cn[0]);
         T* dst = l + 1 < D ? R[l + 1 < D ? l + 1 : 0][M3] : last;
-        const uint32_t zm = EDGE && zero_row_fast(io, yy - l - 1) ? 0u : ~0u;
+        const bool zr = EDGE && zero_row_fast(io, yy - l - 1);
+        const uint32_t zm = zr ? 0u : ~0u;
 #pragma unroll
         for (int j = 0; j < C; ++j) {
             const T c = cn[j];
@@ -274,7 +284,10 @@ __device__ __forceinline__ void row_step_fast(const FastIO<T, C>& io, T*& orow, 
             const T ns = no[j] + so[j];
             const T t = ns + we;
             const T v = update<T, SC>(rt, c, t);
-            dst[j] = EDGE ? keep(v, io.col[RAG ? j : j / VN * VN] & zm) : v;
+            if constexpr (EDGE && kEdgeBranch<T, C, D, RAG>)
+                dst[j] = zr ? T(0) : keep(v, io.col[j / VN * VN]);
+            else
+                dst[j] = EDGE ? keep(v, io.col[RAG ? j : j / VN * VN] & zm) : v;
         }
         rescale_level<T, C, D, SC>(rt, l, dst);
     }
@@ -323,7 +336,7 @@ __device__ __forceinline__ void stream_rows_fast(const FastIO<T, C>& io, T*& oro
     constexpr int W = 2 * D, WF = W / Q, WR = W % Q;
     constexpr int LR = (W - 1) / 2;  // levels the remaining WR rows need (below D)
 #pragma unroll
-    for (int m = 0; m < Q - 3; ++m) load_fast<T, C, EDGE, RAG>(io, ystart + m, Z[m]);
+    for (int m = 0; m < Q - 3; ++m) load_fast<T, C, D, EDGE, RAG>(io, ystart + m, Z[m]);
     int64_t yy = ystart;
     fill_fast<T, C, D, Q, 0, WF, EDGE, RAG, SC>(io, orow, yy, yend, Z, R, rt);
     steps_fast<T, C, D, Q, 0, WR, LR, false, EDGE, RAG, SC>(io, orow, yy, yend, Z, R, rt);

@@ -433,11 +433,11 @@ Form2D choose_form2d(int dtype, int64_t nx, const int64_t* ny, int n, int depth,
     for (int k = 0; k < n; ++k) cells += (double)nx * (double)ny[k];
     if (dtype == 0 && cells >= kStreamCells && stencil2d_supported(dtype, 4, depth)) {
         // 16384^2: 10 steps 556 us at 56 rows per wave and one wave per
-        // workgroup (561 at 64 and four), 8 steps 496 us at 48 and four, 12
+        // workgroup (561 at 64 and four), 8 steps 486 us at 32 and four, 12
         // and 16 steps 754 and 1029 us at 96 and one; shallow passes are bound
         // by their bytes, and most waves fetch them fastest
         f.tile = false;
-        f.g.rows = depth <= 6 ? 24 : (depth <= 8 ? 48 : (depth == 10 ? 56 : 96));
+        f.g.rows = depth <= 6 ? 24 : (depth <= 8 ? 32 : (depth == 10 ? 56 : 96));
         f.g.wpg = depth <= 8 ? 4 : 1;
         const double step = depth <= 8 ? 2.30e-7 : (depth == 10 ? 2.08e-7 : 2.40e-7);
         *us = cells * std::max(depth * step, 1.6e-6);
