@@ -132,10 +132,16 @@ hx_status hx_buffer_create(hx_ctx ctx, size_t bytes, hx_buffer* buf);
  * ownership; hx_buffer_destroy never frees it. */
 hx_status hx_buffer_wrap(hx_ctx ctx, void* dev_ptr, size_t bytes, hx_buffer* buf);
 
+/* Wrap `n` regions in one call (a zero size or null address gives handle 0). */
+hx_status hx_buffer_wrap_many(hx_ctx ctx, int n, void* const* dev_ptrs, const size_t* bytes,
+                              hx_buffer* bufs);
+
 /* Release a buffer handle.  The handle is invalid at once; the memory of an
  * owned buffer is freed only after every submitted operation that uses it has
  * completed. */
 hx_status hx_buffer_destroy(hx_ctx ctx, hx_buffer buf);
+/* The same for `n` handles (0 is skipped); the first error, all tried. */
+hx_status hx_buffer_destroy_many(hx_ctx ctx, int n, const hx_buffer* bufs);
 
 /* Device address and size of a buffer. */
 hx_status hx_buffer_ptr(hx_ctx ctx, hx_buffer buf, void** dev_ptr, size_t* bytes);

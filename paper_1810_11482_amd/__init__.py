@@ -148,6 +148,9 @@ _PROTOS = {
     "hx_buffer_create": (_i32, [_vp, _sz, ctypes.POINTER(_u64)]),
     "hx_buffer_wrap": (_i32, [_vp, _vp, _sz, ctypes.POINTER(_u64)]),
     "hx_buffer_destroy": (_i32, [_vp, _u64]),
+    "hx_buffer_wrap_many": (_i32, [_vp, _i32, ctypes.POINTER(_vp), ctypes.POINTER(_sz),
+                                   ctypes.POINTER(_u64)]),
+    "hx_buffer_destroy_many": (_i32, [_vp, _i32, ctypes.POINTER(_u64)]),
     "hx_buffer_ptr": (_i32, [_vp, _u64, ctypes.POINTER(_vp), ctypes.POINTER(_sz)]),
     "hx_host_alloc": (_i32, [_vp, _sz, ctypes.POINTER(_vp)]),
     "hx_host_free": (_i32, [_vp, _vp]),
@@ -315,6 +318,19 @@ def hx_buffer_wrap(ctx, dev_ptr: int, nbytes: int) -> int:
 
 def hx_buffer_destroy(ctx, buf: int) -> None:
     _ok(ctx, lib.hx_buffer_destroy(ctx, buf))
+
+
+def hx_buffer_wrap_many(ctx, regions):
+    """Handles (a ctypes array) of (address, bytes) regions; empty ones give 0."""
+    n = len(regions)
+    out = (_u64 * n)()
+    _ok(ctx, lib.hx_buffer_wrap_many(ctx, n, (_vp * n)(*[r[0] for r in regions]),
+                                     (_sz * n)(*[r[1] for r in regions]), out))
+    return out
+
+
+def hx_buffer_destroy_many(ctx, bufs) -> None:
+    _ok(ctx, lib.hx_buffer_destroy_many(ctx, len(bufs), bufs))
 
 
 def hx_buffer_ptr(ctx, buf: int):

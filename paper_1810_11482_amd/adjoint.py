@@ -15,20 +15,29 @@ from __future__ import annotations
 
 import torch
 
-from . import (HX_F32, HX_F64, hx_buffer_destroy, hx_buffer_wrap, hx_ctx_create,
+from . import (HX_F32, HX_F64, hx_buffer_destroy_many, hx_buffer_wrap_many, hx_ctx_create,
                hx_event_release, hx_heat_vc_backward, hx_heat_vc_forward, hx_launch_cast64,
                hx_launch_loss, hx_launch_scale, hx_vc_args, hx_vc_schedule)
 
 _CTXS = {}
 
 
+# the current stream's handle without the Stream object around it (1 us of 9,
+# four times per gradient)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _context():
-    stream = torch.cuda.current_stream()
-    key = (stream.device.index, stream.cuda_stream)
+    if _raw_stream is not None:
+        index = torch.cuda.current_device()
+        handle = _raw_stream(index)
+    else:
+        stream = torch.cuda.current_stream()
+        index, handle = stream.device.index, stream.cuda_stream
+    key = (index, handle)
     c = _CTXS.get(key)
     if c is None:
-        c = hx_ctx_create(stream.device.index or 0, compute_streams=1,
-                          external_stream=stream.cuda_stream)
+        c = hx_ctx_create(index or 0, compute_streams=1, external_stream=handle)
         _CTXS[key] = c
     return c
 
@@ -42,22 +51,19 @@ def _dtype_code(t: torch.Tensor) -> int:
 
 
 class _Wrapped:
-    """Non-owning hx buffers over torch tensors for the duration of one call."""
+    """Non-owning hx buffers over torch tensors for the duration of one call, in
+    the tensors' order (all in one call each way: 22 tensors per gradient)."""
 
-    def __init__(self, ctx):
+    def __init__(self, ctx, *tensors):
         self.ctx = ctx
-        self.handles = []
+        self.handles = hx_buffer_wrap_many(ctx, [(t.data_ptr() or None, t.nbytes)
+                                                 for t in tensors])
 
-    def __call__(self, t):
-        if t is None or t.numel() == 0:
-            return 0
-        h = hx_buffer_wrap(self.ctx, t.data_ptr(), t.numel() * t.element_size())
-        self.handles.append(h)
-        return h
+    def __enter__(self):
+        return self.handles
 
-    def close(self):
-        for h in self.handles:
-            hx_buffer_destroy(self.ctx, h)
+    def __exit__(self, *exc):
+        hx_buffer_destroy_many(self.ctx, self.handles)
 
 
 def _check(u0: torch.Tensor, kappa: torch.Tensor):
@@ -81,13 +87,10 @@ class HeatVC(torch.autograd.Function):
         ck = torch.empty((max(nseg - 1, 0), ny, nx), dtype=u0.dtype, device=u0.device)
         work = torch.empty((2 if steps > 1 else 0, ny, nx), dtype=u0.dtype, device=u0.device)
         c = _context()
-        w = _Wrapped(c)
-        try:
-            a = hx_vc_args(_dtype_code(u0), nx, ny, float(dt), int(steps), int(ckpt),
-                           w(u0), w(kappa), w(uT), w(ck), w(work), 0, 0, 0, 0, 0, 0)
+        with _Wrapped(c, u0, kappa, uT, ck, work) as h:
+            a = hx_vc_args(_dtype_code(u0), nx, ny, float(dt), int(steps), int(ckpt), *h,
+                           0, 0, 0, 0, 0, 0)
             hx_event_release(c, hx_heat_vc_forward(c, a))
-        finally:
-            w.close()
         ctx.save_for_backward(u0, kappa, ck)
         ctx.cfg = (float(dt), int(steps), int(ckpt), S)
         return uT
@@ -105,15 +108,11 @@ class HeatVC(torch.autograd.Function):
         work = torch.empty((2 if steps > 1 else 0, ny, nx), dtype=u0.dtype, device=u0.device)
         gk = torch.empty_like(kappa)
         c = _context()
-        w = _Wrapped(c)
-        try:
+        with _Wrapped(c, u0, kappa, ck, work, seg, g, lam0, gk64, gacc, gk) as h:
             code = _dtype_code(u0)
-            a = hx_vc_args(code, nx, ny, dt, steps, ckpt, w(u0), w(kappa), 0, w(ck), w(work),
-                           w(seg), w(g), w(lam0), w(gk64), w(gacc), 0)
+            a = hx_vc_args(code, nx, ny, dt, steps, ckpt, h[0], h[1], 0, *h[2:9], 0)
             hx_event_release(c, hx_heat_vc_backward(c, a))
-            hx_event_release(c, hx_launch_cast64(c, code, nx * ny, w(gk64), w(gk)))
-        finally:
-            w.close()
+            hx_event_release(c, hx_launch_cast64(c, code, nx * ny, h[7], h[9]))
         return lam0, gk, None, None, None
 
 
@@ -130,12 +129,8 @@ class HeatLoss(torch.autograd.Function):
         out = torch.empty((), dtype=torch.float64, device=u.device)
         work = torch.empty(4096, dtype=torch.float64, device=u.device)
         c = _context()
-        w = _Wrapped(c)
-        try:
-            hx_event_release(c, hx_launch_loss(c, _dtype_code(u), u.numel(), w(u), w(y),
-                                               w(resid), w(out), w(work)))
-        finally:
-            w.close()
+        with _Wrapped(c, u, y, resid, out, work) as h:
+            hx_event_release(c, hx_launch_loss(c, _dtype_code(u), u.numel(), *h))
         ctx.save_for_backward(resid)
         return out
 
@@ -145,10 +140,6 @@ class HeatLoss(torch.autograd.Function):
         g = g.to(torch.float64).contiguous().reshape(())
         grad = torch.empty_like(resid)
         c = _context()
-        w = _Wrapped(c)
-        try:
-            hx_event_release(c, hx_launch_scale(c, _dtype_code(resid), resid.numel(), w(resid),
-                                                w(g), w(grad)))
-        finally:
-            w.close()
+        with _Wrapped(c, resid, g, grad) as h:
+            hx_event_release(c, hx_launch_scale(c, _dtype_code(resid), resid.numel(), *h))
         return grad, None

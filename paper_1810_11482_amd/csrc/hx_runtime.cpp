@@ -768,6 +768,31 @@ hx_status hx_buffer_destroy(hx_ctx ctx, hx_buffer h) {
     return HX_OK;
 }
 
+hx_status hx_buffer_wrap_many(hx_ctx ctx, int n, void* const* ptrs, const size_t* bytes,
+                              hx_buffer* out) {
+    Ctx* c = C(ctx);
+    CTX_OR_FAIL(c);
+    if (n < 0 || (n > 0 && (!ptrs || !bytes || !out))) return HX_ERR_ARG;
+    if (c->host_only) return c->fail(HX_ERR_NO_DEVICE, "host-only context");
+    for (int i = 0; i < n; ++i) {
+        out[i] = 0;
+        if (ptrs[i] && bytes[i]) add_buffer(c, ptrs[i], bytes[i], false, &out[i]);
+    }
+    return HX_OK;
+}
+
+hx_status hx_buffer_destroy_many(hx_ctx ctx, int n, const hx_buffer* bufs) {
+    Ctx* c = C(ctx);
+    CTX_OR_FAIL(c);
+    if (n < 0 || (n > 0 && !bufs)) return HX_ERR_ARG;
+    hx_status first = HX_OK;
+    for (int i = 0; i < n; ++i) {
+        const hx_status s = bufs[i] ? hx_buffer_destroy(ctx, bufs[i]) : HX_OK;
+        if (first == HX_OK) first = s;
+    }
+    return first;
+}
+
 hx_status hx_buffer_ptr(hx_ctx ctx, hx_buffer h, void** p, size_t* bytes) {
     Ctx* c = C(ctx);
     CTX_OR_FAIL(c);
