@@ -57,7 +57,7 @@ hx_status check_common(Ctx* c, int dtype, int64_t nx, int64_t ny) {
 hipError_t run_forward(int dt, const VCPass& p, const VCArgs& v, hipStream_t st, void* mid,
                        int64_t stride) {
     return p.waves ? launch_vc_tile(dt, false, p.steps, p.waves, v, mid, stride, nullptr, false,
-                                    nullptr, st)
+                                    nullptr, false, st)
                    : launch_vc_forward(dt, p.steps, v, st, mid, stride);
 }
 
@@ -231,9 +231,13 @@ hx_status hx_heat_vc_backward(hx_ctx ctx, const hx_vc_args* a, const hx_event* d
     return c->submit(
         SC_COMPUTE, deps, ndeps, acc, "heat_vc_backward",
         [=](hipStream_t st) -> hipError_t {
-            hipError_t e = launch_fill(1, pg64, cells, 0.0, st);
-            if (e != hipSuccess) return e;
-            if ((e = launch_fill(dt, pga, cells, 0.0, st)) != hipSuccess) return e;
+            hipError_t e = hipSuccess;
+            // (the fused sweep's first fold starts the total at zero, and every
+            // segment's first pass its accumulator)
+            if (!fused || T == 0) {
+                if ((e = launch_fill(1, pg64, cells, 0.0, st)) != hipSuccess) return e;
+                if ((e = launch_fill(dt, pga, cells, 0.0, st)) != hipSuccess) return e;
+            }
             if (T == 0) return hipMemcpyAsync(pl0, plT, bytes, hipMemcpyDeviceToDevice, st);
             const char* cur = plT;  // the fused sweep's lam_{t+1}
             for (int k = nseg - 1; k >= 0; --k) {
@@ -243,7 +247,7 @@ hx_status hx_heat_vc_backward(hx_ctx ctx, const hx_vc_args* a, const hx_event* d
                 auto ut = [=](int t) -> const char* {
                     return t == t0 ? uck : pseg + (size_t)(t - t0 - 1) * bytes;
                 };
-                const int last = k == nseg - 1 ? 1 : 0;
+                const bool last = k == nseg - 1;
                 if (fused) {  // recompute the segment, fused
                     // states t0+1 .. t1-1 into slots 0 ..
                     const char* src = uck;
@@ -278,8 +282,9 @@ hx_status hx_heat_vc_backward(hx_ctx ctx, const hx_vc_args* a, const hx_event* d
                         // zero, the last folds it into the FP64 total
                         double* total = j + 1 == np ? reinterpret_cast<double*>(pg64) : nullptr;
                         e = p.waves ? launch_vc_tile(dt, true, p.steps, p.waves, v, nullptr, 0, us,
-                                                     j == 0, total, st)
-                                    : launch_vc_adjoint(dt, p.steps, v, us, st, j == 0, total);
+                                                     j == 0, total, last, st)
+                                    : launch_vc_adjoint(dt, p.steps, v, us, st, j == 0, total,
+                                                        last);
                         if (e != hipSuccess) return e;
                         cur = dst;
                         tb -= p.steps;

@@ -469,7 +469,7 @@ constexpr int kVcFusedMax = 4;
 constexpr int kVcTileMax = 12;
 hipError_t launch_vc_tile(int dtype, bool adjoint, int steps, int waves, const VCArgs& v,
                           void* mid, int64_t mid_stride, const void* const* ustates, bool zin,
-                          double* total, hipStream_t stream);
+                          double* total, bool fresh, hipStream_t stream);
 // The passes of a stretch of `steps` steps (kind 0: forward, 1: forward storing
 // every state, 2: adjoint), by modelled time: `waves` of the tile form, or 0:
 // the streaming form.  tiles false: streaming passes only.
@@ -488,11 +488,12 @@ hipError_t launch_vc_forward(int dtype, int steps, const VCArgs& v, hipStream_t 
 // bits as that many launch_vc_step adjoint steps); ustates[k] is u_t of step
 // t = tb - k.  zero_in: the accumulator starts at zero (not read);
 // fold_total: add the accumulator to this FP64 total (the segment's fold)
-// instead of storing it.  The grids vc_fused_supported takes, else
+// instead of storing it, or to zero (fresh: the total is not read).  The grids
+// vc_fused_supported takes, else
 // hipErrorInvalidValue.
 hipError_t launch_vc_adjoint(int dtype, int steps, const VCArgs& v, const void* const* ustates,
                              hipStream_t stream, bool zero_in = false,
-                             double* fold_total = nullptr);
+                             double* fold_total = nullptr, bool fresh = false);
 hipError_t launch_fold(int dtype, void* acc, double* total, int64_t n, hipStream_t stream);
 hipError_t launch_fill(int dtype, void* p, int64_t n, double v, hipStream_t stream);
 hipError_t launch_cast64(int dtype, const double* src, void* dst, int64_t n, hipStream_t stream);

@@ -141,6 +141,7 @@ struct VCDev {
     double dt;
     int rows;
     int aligned;        // every row starts 16-byte aligned
+    int fresh;          // fused adjoint, FOLD: the FP64 total starts at zero (not read)
 };
 
 // Weighted face sum sum_f kappa_f (f_n - f_c) for the lane's C cells of row y.
@@ -745,7 +746,8 @@ __global__ __launch_bounds__(256) void k_vc_fwd(VCDev a, int64_t nstrips, int64_
 // steps.  Faces, rings and edge rules as in k_vc_fwd; a gradient term across
 // an edge face reads u_c lam_c, as the single step's.  ZIN: the pass opens a
 // checkpoint segment, whose accumulator starts at zero (not read).  FOLD: the
-// pass closes the segment: the accumulator's rows are added to the FP64 total
+// pass closes the segment: the accumulator's rows are added to the FP64 total (or
+// to zero: a.fresh)
 // (as the fold of a segment does) instead of being stored.
 struct UStates {
     const void* p[4];
@@ -901,7 +903,8 @@ __global__ __launch_bounds__(256) void k_vc_adj(VCDev a, UStates us, double* __r
                 double* tp = total + r * nx + xl;
 #pragma unroll
                 for (int j = 0; j < C; ++j)
-                    if (!RAG || ln.in[j]) tp[j] += (double)gr[m6(P - D)][j];
+                    if (!RAG || ln.in[j])
+                        tp[j] = (a.fresh ? 0.0 : tp[j]) + (double)gr[m6(P - D)][j];
             }
         } else {
             store_lane_if<T, RAG, ST_NT>(rsg, ln, lane_off, rout, r, nx, gr[m6(P - D)]);
@@ -1052,7 +1055,7 @@ hipError_t launch_vc_forward(int dtype, int steps, const VCArgs& v, hipStream_t 
 }
 
 hipError_t launch_vc_adjoint(int dtype, int steps, const VCArgs& v, const void* const* ustates,
-                             hipStream_t st, bool zero_in, double* fold_total) {
+                             hipStream_t st, bool zero_in, double* fold_total, bool fresh) {
     if (steps < 1 || steps > C || steps > 4 || !v.lam || !v.gacc || !vc_fused_supported(dtype, v))
         return hipErrorInvalidValue;
     UStates us{};
@@ -1060,7 +1063,7 @@ hipError_t launch_vc_adjoint(int dtype, int steps, const VCArgs& v, const void* 
         if (!ustates[k]) return hipErrorInvalidValue;
         us.p[k] = ustates[k];
     }
-    VCDev a{nullptr, v.kappa, v.lam, v.out, v.gacc, v.nx, v.ny, v.dt, 0, 1};
+    VCDev a{nullptr, v.kappa, v.lam, v.out, v.gacc, v.nx, v.ny, v.dt, 0, 1, fresh ? 1 : 0};
     const int variant = (zero_in ? 1 : 0) | (fold_total ? 2 : 0);
     const void* k = fused_kernel(dtype, v.nx, true, steps, variant);
     return launch_fused(k, a, steps, v.rows, &us, &fold_total, true, st);

@@ -76,8 +76,8 @@ struct VCTile {
     int64_t stride;
     const void* us[kVcTileMax];  // ADJ: u_t of each step
     void* gacc;                  // ADJ: the accumulator (not read when zin; not stored when
-    double* total;               // total is given: added there instead)
-    int zin;
+    double* total;               // total is given: added there instead, or to zero: fresh)
+    int zin, fresh;
     int64_t nx, ny;
     double dt;
     int steps, halo;
@@ -377,7 +377,10 @@ __device__ __forceinline__ void tile_run(const VCTile& a, const Place& p, int64_
             if (a.total) {
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
-                    if (p.store[j]) a.total[y * p.nx + p.x + j] += (double)g[r][j];
+                    if (p.store[j]) {
+                        double* tp = a.total + y * p.nx + p.x + j;
+                        *tp = (a.fresh ? 0.0 : *tp) + (double)g[r][j];
+                    }
             } else {
                 store4<T>(static_cast<T*>(a.gacc), p, y, g[r]);
             }
@@ -531,7 +534,7 @@ std::vector<VCPass> choose_vc_passes(int dtype, int kind, int64_t nx, int64_t ny
 
 hipError_t launch_vc_tile(int dtype, bool adjoint, int steps, int waves, const VCArgs& v,
                           void* mid, int64_t mid_stride, const void* const* ustates, bool zin,
-                          double* total, hipStream_t st) {
+                          double* total, bool fresh, hipStream_t st) {
     VCTile a{};
     a.f = adjoint ? v.lam : v.u;
     a.kappa = v.kappa;
@@ -541,6 +544,7 @@ hipError_t launch_vc_tile(int dtype, bool adjoint, int steps, int waves, const V
     a.gacc = v.gacc;
     a.total = total;
     a.zin = zin ? 1 : 0;
+    a.fresh = fresh ? 1 : 0;
     a.nx = v.nx;
     a.ny = v.ny;
     a.dt = v.dt;

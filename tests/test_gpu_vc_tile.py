@@ -31,3 +31,26 @@ def test_tile_equals_streaming(ctx, dtype, shape):
         got = gradient(ctx, shape, dtype, T, S, T % 4, 0)
         for x, y in zip(got, want):
             assert np.array_equal(x, y), (T, S)
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("rows", [0, 8])
+def test_totals_start_at_zero(ctx, dtype, rows):
+    """The FP64 total and the accumulator may hold anything beforehand, also on
+    a second run over the same buffers."""
+    from test_gpu_vc_ragged import Dev, fields
+    shape, T, S = (40, 241), 13, 6
+    want = gradient(ctx, shape, dtype, T, S, 0, rows)[2]
+    u0, kap, lam = fields(shape, dtype)
+    d = Dev(ctx, shape, dtype, 0)
+    code = hx.HX_F64 if dtype == np.float64 else hx.HX_F32
+    seg, nseg = hx.hx_vc_schedule(T, S)
+    bad = np.full(shape, np.nan)
+    a = hx.hx_vc_args(code, shape[1], shape[0], 0.2, T, S, d.new(1, u0), d.new(1, kap), d.new(1),
+                      d.new(nseg - 1), d.new(2), d.new(seg - 1), d.new(1, lam), d.new(1),
+                      d.new(1, bad, es=8), d.new(1, bad.astype(dtype)), rows)
+    for _ in range(2):
+        e = hx.hx_heat_vc_backward(ctx, a, [hx.hx_heat_vc_forward(ctx, a)])
+        assert hx.hx_wait(ctx, e) == hx.HX_OK, hx.hx_last_error(ctx)
+        assert np.array_equal(d.get(a.gk64, np.float64), want)
+    d.close()
