@@ -135,6 +135,7 @@ const char* prop_unfit(const Seg1D& s, int D) {
 // counted as half a workgroup's cells at least), and each segment's first
 // workgroups wait for its description (5 ns).
 std::vector<LineSeg> line_segments(const std::vector<Seg1D>& segs, int D, double direct_us) {
+    if (segs.size() > 65536) return {};  // 1 KB of taps and ends each
     int64_t cells = 0, wgs = 0;
     double rmax = 0.0;
     for (const Seg1D& s : segs) {

@@ -505,31 +505,30 @@ double pass_us(int dtype, int kind, int64_t nx, int64_t ny, int d, int* waves) {
 std::vector<VCPass> choose_vc_passes(int dtype, int kind, int64_t nx, int64_t ny, int steps,
                                      bool tiles) {
     // np passes as even as they can be, np by the least modelled time
-    std::vector<VCPass> best;
-    if (steps < 1) return best;
+    std::vector<VCPass> passes;
+    if (steps < 1) return passes;
     const int deepest = dtype && kind == 2 ? 2 : kVcFusedMax;
-    double best_us = 0.0;
-    auto split = [&](int np, bool tile, double* us) {
-        std::vector<VCPass> p;
-        *us = 0.0;
-        for (int j = 0; j < np; ++j) {
-            VCPass q{steps / np + (j < steps % np ? 1 : 0), 0};
-            if (tile) *us += pass_us(dtype, kind, nx, ny, q.steps, &q.waves);
-            p.push_back(q);
-        }
-        return p;
-    };
-    if (!tiles) return split((steps + deepest - 1) / deepest, false, &best_us);
-    for (int np = (steps + kVcTileMax - 1) / kVcTileMax; np <= (steps + deepest - 1) / deepest;
-         ++np) {
-        double us;
-        std::vector<VCPass> p = split(np, true, &us);
-        if (best.empty() || us < best_us) {
-            best = p;
-            best_us = us;
+    const int most = (steps + deepest - 1) / deepest;
+    double us[kVcTileMax + 1] = {};
+    int waves[kVcTileMax + 1] = {};
+    int best = most;
+    if (tiles) {
+        for (int d = 1; d <= kVcTileMax; ++d) us[d] = pass_us(dtype, kind, nx, ny, d, &waves[d]);
+        double best_us = std::numeric_limits<double>::infinity();
+        for (int np = (steps + kVcTileMax - 1) / kVcTileMax; np <= most; ++np) {
+            const int d = steps / np, more = steps % np;
+            const double t = (np - more) * us[d] + (more ? more * us[d + 1] : 0.0);
+            if (t < best_us) {
+                best = np;
+                best_us = t;
+            }
         }
     }
-    return best;
+    for (int j = 0; j < best; ++j) {
+        const int d = steps / best + (j < steps % best ? 1 : 0);
+        passes.push_back(VCPass{d, waves[d]});
+    }
+    return passes;
 }
 
 hipError_t launch_vc_tile(int dtype, bool adjoint, int steps, int waves, const VCArgs& v,
