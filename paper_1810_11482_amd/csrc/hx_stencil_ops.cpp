@@ -135,23 +135,30 @@ static hx_status launch_1d(Ctx* c, const hx_stencil_args* a, const hx_event* dep
     const int vn = vec_cells(dt);
     const bool cell_aligned = (((uintptr_t)pin | (uintptr_t)pout | (uintptr_t)ptmp |
                                 (uintptr_t)plo | (uintptr_t)phi) & (es - 1)) == 0;
-    std::vector<Pass1D> how;
+    struct Step {
+        Geom1D g;
+        int prop;  // index into props, or -1
+    };
+    std::vector<Step> how;
+    std::vector<PropLine> props;
     for (int d : plan) {
-        Pass1D ps{};
+        Step ps{g, -1};
+        ps.g.steps = d;
+        ps.g.halo = std::max(vn, round_up(d, vn));
         if (choose && d <= max_time_block_1d(dt, 16)) {
-            ps = choose_pass1d(dt, a->r, &n, 1, d, ghost);
-            ps.prop = ps.prop && cell_aligned;
-        } else {
-            ps.g = g;
-            ps.g.steps = d;
-            ps.g.halo = std::max(vn, round_up(d, vn));
+            const Pass1D c1 = choose_pass1d(dt, a->r, &n, 1, d, ghost);
+            ps.g = c1.g;
+            if (c1.prop && cell_aligned) {
+                ps.prop = (int)props.size();
+                props.push_back(c1.pl);
+            }
         }
         how.push_back(ps);
     }
     std::string what = "stencil1d n=" + std::to_string(n) + " steps=" + std::to_string(a->steps);
     return c->submit(
         SC_COMPUTE, deps, ndeps, acc, what,
-        [=](hipStream_t st) -> hipError_t {
+        [=, how = std::move(how), props = std::move(props)](hipStream_t st) -> hipError_t {
             // passes ping-pong so that the last one lands in out
             const char* src = pin;
             for (int p = 0; p < passes; ++p) {
@@ -159,8 +166,8 @@ static hx_status launch_1d(Ctx* c, const hx_stencil_args* a, const hx_event* dep
                 Seg1D sg = seg;
                 sg.in = src;
                 sg.out = dst;
-                hipError_t e = how[p].prop ? launch_prop_pass(sg, how[p].pl, st)
-                                           : launch_stencil1d(dt, sg, how[p].g, st);
+                hipError_t e = how[p].prop >= 0 ? launch_prop_pass(sg, props[how[p].prop], st)
+                                                : launch_stencil1d(dt, sg, how[p].g, st);
                 if (e != hipSuccess) return e;
                 src = dst;
             }
