@@ -57,6 +57,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 KERNELS = {
     "direct": ("stencil1d_flat_2p28_fp32_traffic.md",
                ("paper_1810_11482_amd/csrc/hx_stencil1d.hip",
+                "paper_1810_11482_amd/csrc/hx_line.hpp",
                 "paper_1810_11482_amd/csrc/hx_internal.h")),
     "propagator": ("prop1d_2p28_fp32_traffic.md",
                    ("paper_1810_11482_amd/csrc/hx_prop1d.hip",
