@@ -394,8 +394,9 @@ constexpr double kStreamCells = 1.0e8;
 constexpr int kTileMax = 24;  // deepest tile pass considered
 
 // Below that, and in double, the streaming form takes passes of up to 8 steps
-// where it is modelled faster, with few rows per wave (16, 24 or 32: more waves
-// and shorter chains against up to a doubling of the work).  t = a + max(S (l0 +
+// (float: 10, too) where it is modelled faster, with few rows per wave (16, 24
+// or 32, at 10 steps up to 64: more waves and shorter chains against up to a
+// doubling of the work).  t = a + max(S (l0 +
 // D l), q (S m + (rows + D) D i), bytes) (1 + rag) + c min(the last two), with
 // S = rows + 2 D row steps, w the waves per SIMD and q w rounded up half way
 // while it is small, bytes = 2 per cell at bw (1 + h / w).  Fitted to passes of
@@ -403,7 +404,8 @@ constexpr int kTileMax = 24;  // deepest tile pass considered
 // and in bands (mean deviation 7-8 %).  Measured, stream / tile: 4096^2 in 16
 // bands, 4 steps, 35 / 42 us float, 55 / 63 double; 9000 x 2300 in 23 bands, 6
 // steps, 54 / 69 and 99 / 127; 10001 x 10000, 8 steps, double 398 / 491;
-// 2048^2, 4 steps, 20.8 / 17.7; 8192^2, 4 steps, 127 / 119.
+// 2048^2, 4 steps, 20.8 / 17.7; 8192^2, 4 steps, 127 / 119; 5070 x 16192 in 5
+// bands, 10 steps, 195 / 226.
 struct StreamCost {
     double a, l0, l, m, i, bw, rag, h, c;
 };
@@ -459,8 +461,10 @@ Form2D choose_form2d(int dtype, int64_t nx, const int64_t* ny, int n, int depth,
             f.g.wpg = c.wpg;
         }
     }
-    for (int rows : {16, 24, 32}) {
-        if (depth < 1 || depth > 8 || !stencil2d_supported(dtype, 4, depth)) break;
+    static const int kRows[2][3] = {{16, 24, 32}, {24, 32, 64}};
+    for (int rows : kRows[depth == 10]) {
+        if (depth < 1 || (depth > 8 && depth != 10) || !stencil2d_supported(dtype, 4, depth))
+            break;
         int64_t waves = 0;
         for (int k = 0; k < n; ++k) waves += strips * ((ny[k] + rows - 1) / rows);
         const double t = stream_us(dtype, nx, waves, cells, depth, rows);
