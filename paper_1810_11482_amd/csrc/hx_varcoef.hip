@@ -26,6 +26,7 @@
 #include <vector>
 
 #include "hx_internal.h"
+#include "hx_vcstrip.hpp"
 
 namespace hx {
 namespace {
@@ -46,7 +47,7 @@ __device__ __forceinline__ double dpp_move(double x) {
 __device__ __forceinline__ float fmaT(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fmaT(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
-constexpr int C = 4;  // cells per lane
+constexpr int C = kVcCols;  // cells per lane
 constexpr int S = 64 * C;
 
 // One row of one field as seen by a lane: its C cells plus the cells just west
@@ -466,6 +467,7 @@ template <typename T, bool RAG>
 struct Lane {
     int64_t xl;       // first column
     bool lin;         // some of the lane's cells lie inside the domain
+    bool own;         // the lane stores its inside cells (hx_vcstrip.hpp)
     bool wok, eok;    // cell 0's west face, cell C-1's east face is interior
     bool part;        // RAG: the lane's cells straddle the row's end
     bool in[C];       // RAG: the cell lies inside
@@ -474,10 +476,11 @@ struct Lane {
 };
 
 template <typename T, bool RAG>
-__device__ __forceinline__ Lane<T, RAG> make_lane(int64_t xl, int64_t nx) {
+__device__ __forceinline__ Lane<T, RAG> make_lane(int lane, int64_t xl, int64_t nx) {
     Lane<T, RAG> l;
     l.xl = xl;
     l.lin = xl >= 0 && (RAG ? xl < nx : xl + C <= nx);
+    l.own = l.lin && vc_lane_stores(lane, xl, nx);
     l.wok = xl >= 1;
     l.eok = xl + C < nx;
     l.part = RAG && l.lin && xl + C > nx;
@@ -541,8 +544,9 @@ __device__ __forceinline__ void store_cell(__amdgpu_buffer_rsrc_t rs, double v, 
 }
 
 // store_row_if for the fused passes: `off` is the offset of a lane whose cells
-// are all stored (else out of range); a straddling lane stores its inside
-// cells one by one, in the waves that have one.
+// are all stored (else out of range); a straddling lane that stores at all (the
+// halo lane of the strip before holds the same cells) stores its inside cells
+// one by one, in the waves that have one.
 template <typename T, bool RAG, int AUX = 0>
 __device__ __forceinline__ void store_lane_if(__amdgpu_buffer_rsrc_t rs, const Lane<T, RAG>& l,
                                               uint32_t off, bool ok, int64_t y, int64_t nx,
@@ -553,7 +557,7 @@ __device__ __forceinline__ void store_lane_if(__amdgpu_buffer_rsrc_t rs, const L
 #pragma unroll
             for (int j = 0; j < C; ++j)
                 store_cell(rs, v[j],
-                           ok && l.part && l.in[j]
+                           ok && l.own && l.part && l.in[j]
                                ? (uint32_t)((y * nx + l.xl + j) * (int64_t)sizeof(T))
                                : OOB_OFFSET);
         }
@@ -603,7 +607,6 @@ template <typename T, int D, bool MID, bool RAG>
 __global__ __launch_bounds__(256) void k_vc_fwd(VCDev a, int64_t nstrips, int64_t nwaves,
                                                 void* mid, int64_t mid_stride) {
     static_assert(D >= 1 && D <= C && D <= 5, "the halo lane covers at most C steps");
-    constexpr int W = S - 2 * C;  // output columns per strip
     const int wpg = blockDim.x >> 6;
     const int64_t wave = (int64_t)xcd_block(blockIdx.x, gridDim.x) * wpg +
                          __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -611,13 +614,13 @@ __global__ __launch_bounds__(256) void k_vc_fwd(VCDev a, int64_t nstrips, int64_
     const int lane = threadIdx.x & 63;
     const int64_t strip = wave % nstrips, chunk = wave / nstrips;
     const int64_t nx = a.nx, ny = a.ny;
-    const int64_t xl = strip * W - C + (int64_t)lane * C;  // this lane's first column
+    const int64_t xl = vc_lane_column(strip, lane);  // this lane's first column
     const int64_t y0 = chunk * a.rows;
     const int64_t y1 = (y0 + a.rows < ny) ? y0 + a.rows : ny;
     const T dt = static_cast<T>(a.dt);
     const T* U = static_cast<const T*>(a.u);
     const T* K = static_cast<const T*>(a.kappa);
-    const Lane<T, RAG> ln = make_lane<T, RAG>(xl, nx);
+    const Lane<T, RAG> ln = make_lane<T, RAG>(lane, xl, nx);
     // row y of f for this lane.  A pass reads each row once (a chunk's halo
     // rows twice); nontemporal loads measured faster where the pass stores one
     // row per row read (5.3 against 4.4 TB/s), cached loads where it stores
@@ -628,9 +631,8 @@ __global__ __launch_bounds__(256) void k_vc_fwd(VCDev a, int64_t nstrips, int64_
     const int bytes = (int)(ny * nx * (int64_t)sizeof(T));
     const __amdgpu_buffer_rsrc_t rso =
         __builtin_amdgcn_make_buffer_rsrc(a.out, (short)0, bytes, BUF_DWORD3);
-    const bool store_lane = lane >= 1 && lane <= 62 && ln.lin;
     const uint32_t lane_off =
-        store_lane && !ln.part ? (uint32_t)(xl * (int64_t)sizeof(T)) : OOB_OFFSET;
+        ln.own && !ln.part ? (uint32_t)(xl * (int64_t)sizeof(T)) : OOB_OFFSET;
     __amdgpu_buffer_rsrc_t rsm[D > 1 ? D - 1 : 1];
     if constexpr (MID)
 #pragma unroll
@@ -757,7 +759,6 @@ template <typename T, int D, bool ZIN, bool FOLD, bool RAG>
 __global__ __launch_bounds__(256) void k_vc_adj(VCDev a, UStates us, double* __restrict__ total,
                                                 int64_t nstrips, int64_t nwaves) {
     static_assert(D >= 1 && D <= C && D <= 4, "the halo lane covers at most C steps");
-    constexpr int W = S - 2 * C;  // output columns per strip
     const int wpg = blockDim.x >> 6;
     const int64_t wave = (int64_t)xcd_block(blockIdx.x, gridDim.x) * wpg +
                          __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -765,14 +766,14 @@ __global__ __launch_bounds__(256) void k_vc_adj(VCDev a, UStates us, double* __r
     const int lane = threadIdx.x & 63;
     const int64_t strip = wave % nstrips, chunk = wave / nstrips;
     const int64_t nx = a.nx, ny = a.ny;
-    const int64_t xl = strip * W - C + (int64_t)lane * C;  // this lane's first column
+    const int64_t xl = vc_lane_column(strip, lane);  // this lane's first column
     const int64_t y0 = chunk * a.rows;
     const int64_t y1 = (y0 + a.rows < ny) ? y0 + a.rows : ny;
     const T dt = static_cast<T>(a.dt);
     const T* L = static_cast<const T*>(a.lam);
     const T* K = static_cast<const T*>(a.kappa);
     const T* G = static_cast<const T*>(a.gacc);
-    const Lane<T, RAG> ln = make_lane<T, RAG>(xl, nx);
+    const Lane<T, RAG> ln = make_lane<T, RAG>(lane, xl, nx);
     auto raw = [&](const T* f, int64_t y, T (&v)[C]) {
         load_lane<T, RAG, false>(f, ln, y, nx, ny, v);
     };
@@ -781,9 +782,8 @@ __global__ __launch_bounds__(256) void k_vc_adj(VCDev a, UStates us, double* __r
         __builtin_amdgcn_make_buffer_rsrc(a.out, (short)0, bytes, BUF_DWORD3);
     const __amdgpu_buffer_rsrc_t rsg =
         __builtin_amdgcn_make_buffer_rsrc(a.gacc, (short)0, bytes, BUF_DWORD3);
-    const bool store_lane = lane >= 1 && lane <= 62 && ln.lin;
     const uint32_t lane_off =
-        store_lane && !ln.part ? (uint32_t)(xl * (int64_t)sizeof(T)) : OOB_OFFSET;
+        ln.own && !ln.part ? (uint32_t)(xl * (int64_t)sizeof(T)) : OOB_OFFSET;
 
     T lr[D][3][C];    // lam of level k (level 0: lam_{tb+1})
     T ur[D][3][C];    // u_t read by level k + 1
@@ -899,7 +899,7 @@ __global__ __launch_bounds__(256) void k_vc_adj(VCDev a, UStates us, double* __r
         const bool rout = r >= y0 && r < y1;
         store_lane_if<T, RAG, ST_NT>(rso, ln, lane_off, rout, r, nx, out);
         if constexpr (FOLD) {
-            if (rout && store_lane) {
+            if (rout && ln.own) {
                 double* tp = total + r * nx + xl;
 #pragma unroll
                 for (int j = 0; j < C; ++j)
@@ -1031,7 +1031,7 @@ int fill_rows(const void* k, int64_t nstrips, int64_t ny, int depth) {
 hipError_t launch_fused(const void* k, VCDev a, int depth, int rows_req, void* arg3, void* arg4,
                         bool adjoint, hipStream_t st) {
     if (!k) return hipErrorInvalidValue;
-    int64_t nstrips = (a.nx + (S - 2 * C) - 1) / (S - 2 * C);
+    int64_t nstrips = vc_strips(a.nx);
     a.rows = rows_req > 0 ? rows_req : fill_rows(k, nstrips, a.ny, depth);
     int64_t nwaves = nstrips * ((a.ny + a.rows - 1) / a.rows);
     const int wpg = 4;
