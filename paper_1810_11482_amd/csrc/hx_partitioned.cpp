@@ -96,6 +96,16 @@ hx_status run_bands_batched(Ctx* c, const hx_partitioned_desc* d, hx_event gate,
     for (int depth : plan)
         if (!stencil2d_supported(dt, g.cpl, depth))
             return c->fail(HX_ERR_ARG, "unsupported 2D pass depth " + std::to_string(depth));
+    // a band's pass reads rows of `in` after it has stored rows of `out`
+    for (int p = 0; p < P && !plan.empty(); ++p) {
+        const size_t bytes = (size_t)(d->sizes[p] * d->nx * es);
+        char* q = nullptr;
+        Access a{}, b{};
+        hx_status s = resolve_range(c, d->bufs_a[p], 0, bytes, &q, &a, true);
+        if (!s) s = resolve_range(c, d->bufs_b[p], 0, bytes, &q, &b, true);
+        if (s) return s;
+        if (a.buf_slot == b.buf_slot) return c->fail(HX_ERR_ARG, "in and out overlap");
+    }
     const int groups = (P + kMaxBands - 1) / kMaxBands;
     std::vector<hx_event> prev, cur;
     if (gate) {
