@@ -119,9 +119,13 @@ __device__ __forceinline__ float line_cell(const Part& s, int64_t c) {
 }
 
 // Cells c .. c + 3.  Four cells on one side of both ends are one load (of the
-// reflection, reversed); only a group that straddles an end takes its cells
-// one by one (each a round trip to memory: with all groups of an end's block
-// taken so, a batch of 4096 short segments ran at half speed).
+// reflection, reversed); only a group that straddles an end, or the far end of
+// a halo, takes its cells one by one (each a round trip to memory: with all
+// groups of an end's block taken so, a batch of 4096 short segments ran at half
+// speed).  A group wholly past a halo loads the halo's last four cells.
+// (Reflected cells are in reach up to D <= n from the end, so the clamp to the
+// run meets none that a tap of the window does: those are at most 95 cells
+// away, and the run has at least 256.)
 __device__ __forceinline__ f32x4 line_cells4(const Part& s, int64_t c, bool inside) {
     typedef __attribute__((address_space(1))) const f32x4u G;
     if (inside) return *(G*)(s.in + c);
@@ -132,7 +136,7 @@ __device__ __forceinline__ f32x4 line_cells4(const Part& s, int64_t c, bool insi
         if (s.lo) {
             base = s.lo;
             at = s.hw + c < 0 ? 0 : s.hw + c;
-            whole = s.hw >= 4;
+            whole = s.hw + c >= 0 || (s.hw + c <= -4 && s.hw >= 4);
         } else {
             flip = true;
             at = -c - 5 < s.n - 4 ? -c - 5 : s.n - 4;
@@ -143,7 +147,7 @@ __device__ __forceinline__ f32x4 line_cells4(const Part& s, int64_t c, bool insi
         if (s.hi) {
             base = s.hi;
             at = k < s.hw - 4 ? k : s.hw - 4;
-            whole = s.hw >= 4;
+            whole = k + 4 <= s.hw || (k >= s.hw && s.hw >= 4);
         } else {
             flip = true;
             at = s.n - 3 - k > 0 ? s.n - 3 - k : 0;
