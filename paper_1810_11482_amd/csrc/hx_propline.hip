@@ -57,7 +57,11 @@ constexpr int kReach = 256;       // deepest pass
 // The shallowest pass the library takes in this form.  From here on its error
 // against 64 bits is the smaller one on positive noise and on smooth fields at
 // every rate measured (r = 1/20 .. 1/4, 12 to 200 steps: 0.46-0.64e-7 against
-// 0.56-10e-7), per cell also on noise of both signs.
+// 0.56-10e-7), per cell also on noise of both signs.  The worst cell of combs of
+// lone values, of spikes in noise and of log-normal noise, 300 rates from 1/1000
+// to 1/4 and depths from 20 to 256 worked out in the products' own arithmetic:
+// 4.9e-7, and no larger than stepping's of the same field but for 4 in 8474
+// (by at most an eighth).
 constexpr int kPropMinDepth = 20;
 constexpr int kEdge = 320;        // cells a block may read on each side (the window and 256)
 constexpr float kMaxF = 3.402823466e38f;
@@ -554,16 +558,16 @@ bool propline_setup(double r, int D, PropLine* out, int min_H) {
     out->texp = texp;
     out->chk = (float)std::ldexp(E, 21 + texp);
     std::memset(out->tap, 0, sizeof out->tap);
-    // (a tap's rounding is handed on to the next one out, whose lower half is
-    // finer, so that the rounded taps still sum to 1: a smooth field meets the
-    // sum of the roundings)
+    // (each tap is rounded by itself: its two halves are within 2^-23 of it.
+    // Handing the roundings on to the next tap out, so that the rounded taps sum
+    // to 1, gave a smooth field 10 % less error at r = 1/20, and cells that only
+    // the next, far smaller tap reaches up to 3.9e-6)
     const double scale = std::ldexp(1.0, texp);
-    double carry = 0.0;
     for (int j = 0; j <= std::min(K, H + 31); ++j) {
-        const double x = p[j] * scale + carry;
+        const double x = p[j] * scale;
         uint16_t hi, lo;
-        const float xh = to_half((float)x, &hi), xl = to_half((float)(x - xh), &lo);
-        carry = (x - xh - xl) * (j ? 1.0 : 0.5);
+        const float xh = to_half((float)x, &hi);
+        to_half((float)(x - xh), &lo);
         for (int k : {H + 31 + j, H + 31 - j}) {
             if (k >= 8 * units_of(NC) + 8) continue;
             out->tap[0][k] = hi;
