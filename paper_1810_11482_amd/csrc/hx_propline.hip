@@ -180,19 +180,27 @@ __device__ __forceinline__ float far4(const f32x4& x) {
 
 // The stepping path of one block: its cells c0 .. c0 + 1023 advanced D steps
 // over the window of 256 cells on each side, 24 consecutive cells per lane, in
-// the rescaled direct form.
+// the rescaled direct form.  Past a zero-Dirichlet end the cells are 0 and reset
+// after every step, as there (the reflection's ghost cell, the sum of opposite
+// cells, would be NaN beside an infinity).
 __device__ __forceinline__ void step_line(const Part& s, const PropLine& pl, int64_t c0) {
     constexpr int K = 24;
     const int l = threadIdx.x & 63;
     const int64_t b = c0 - kReach + (int64_t)K * l;
     float a[K];
+    const int64_t n = s.n;
+    const bool zero_lo = !s.lo && c0 < kReach;
+    const bool zero_hi = !s.hi && c0 + 1024 + kReach > n;
 #pragma unroll
-    for (int t = 0; t < K; ++t) a[t] = line_cell(s, b + t);
+    for (int t = 0; t < K; ++t) {
+        const int64_t c = b + t;
+        a[t] = (zero_lo && c < 0) || (zero_hi && c >= n) ? 0.f : line_cell(s, c);
+    }
     const float beta = pl.beta, ap = pl.ap;
     const int D = pl.D, period = pl.period;
     int since = 0;
     for (int k = 0; k < D; ++k) {
-        step_tile_scaled<float, K>(a, beta, false, false, 0, 0);
+        step_tile_scaled<float, K>(a, beta, zero_lo, zero_hi, b, n);
         if (++since == period) {
             since = 0;
             scale_tile<float, K>(a, ap);
@@ -202,7 +210,7 @@ __device__ __forceinline__ void step_line(const Part& s, const PropLine& pl, int
 #pragma unroll
     for (int t = 0; t < K; ++t) {
         const int64_t c = b + t;
-        if (c >= c0 && c < c0 + 1024 && c >= 0 && c < s.n) s.out[c] = a[t];
+        if (c >= c0 && c < c0 + 1024 && c >= 0 && c < n) s.out[c] = a[t];
     }
 }
 
