@@ -61,6 +61,22 @@ hipError_t run_forward(int dt, const VCPass& p, const VCArgs& v, hipStream_t st,
                    : launch_vc_forward(dt, p.steps, v, st, mid, stride);
 }
 
+// Whether [a, a + n) and [b, b + n) share a byte.
+bool overlap(const char* a, const char* b, size_t n) { return a < b + n && b < a + n; }
+
+// The passes of a stretch that leaves its input where its output goes (kinds as
+// choose_vc_passes): at least two, since a pass reads its input's rows while it
+// stores its output's.  (A single step has no such form.)
+std::vector<VCPass> passes_in_place(int dtype, int kind, int64_t nx, int64_t ny, int steps,
+                                    bool tiles) {
+    std::vector<VCPass> all = choose_vc_passes(dtype, kind, nx, ny, steps, tiles);
+    if (steps < 2 || all.size() > 1) return all;
+    all = choose_vc_passes(dtype, kind, nx, ny, (steps + 1) / 2, tiles);
+    for (const VCPass& p : choose_vc_passes(dtype, kind, nx, ny, steps / 2, tiles))
+        all.push_back(p);
+    return all;
+}
+
 }  // namespace
 
 #define LOCK_CTX(ctx)                                  \
@@ -148,7 +164,9 @@ hx_status hx_heat_vc_forward(hx_ctx ctx, const hx_vc_args* a, const hx_event* de
     std::vector<VCPass> full, tail;  // of a whole stretch, and of the last one
     if (fused) {
         full = choose_vc_passes(dt, 0, nx, ny, S, rows <= 0);
-        tail = choose_vc_passes(dt, 0, nx, ny, T - (sc.nseg - 1) * S, rows <= 0);
+        const bool in_place = sc.nseg == 1 && overlap(pu0, puT, bytes);
+        tail = (in_place ? passes_in_place : choose_vc_passes)(dt, 0, nx, ny,
+                                                               T - (sc.nseg - 1) * S, rows <= 0);
     }
     return c->submit(SC_COMPUTE, deps, ndeps, acc, "heat_vc_forward",
                      [=](hipStream_t st) -> hipError_t {
@@ -226,7 +244,8 @@ hx_status hx_heat_vc_backward(hx_ctx ctx, const hx_vc_args* a, const hx_event* d
     for (int q = 0; fused && q < 2; ++q) {
         const int L = q ? T - (nseg - 1) * S : S;
         re[q] = choose_vc_passes(dt, 1, nx, ny, L - 1, rows <= 0);
-        adj[q] = choose_vc_passes(dt, 2, nx, ny, L, rows <= 0);
+        const bool in_place = nseg == 1 && overlap(plT, pl0, bytes);
+        adj[q] = (in_place ? passes_in_place : choose_vc_passes)(dt, 2, nx, ny, L, rows <= 0);
     }
     return c->submit(
         SC_COMPUTE, deps, ndeps, acc, "heat_vc_backward",
