@@ -260,9 +260,9 @@ typedef struct {
  * streams.  When no node can be observed (node_events is null, the context has
  * no hazard checker and no injected failure, no graph is being captured) a
  * pass is launched whole, in groups of up to 64 partitions (16 bands), each
- * launch depending on every one of the previous pass: the same results (f32: to
- * rounding) without the host work per node.  HX_PART_PLAIN: the comparator: one step per launch, issued in
- * Algorithm 1's order and chained on one stream.  HX_PART_BATCHED (2D bands
+ * launch depending on every one of the previous pass: the same bits without the
+ * host work per node.  HX_PART_PLAIN: the comparator: one step per launch,
+ * issued in Algorithm 1's order and chained on one stream.  HX_PART_BATCHED (2D bands
  * only): every pass is one launch per group of up to 16 bands (one node per
  * launch, depending on every node of the previous pass); 1D partitions batch
  * through hx_plan_create_batched.  `deps` gate the first pass.

@@ -212,20 +212,48 @@ hx_status run_bands_batched(Ctx* c, const hx_partitioned_desc* d, hx_event gate,
     return s;
 }
 
+// The form and geometry of a pass of `depth` steps over each group of up to
+// kMaxParts 1D partitions.  Whether a group takes the propagator form decides
+// its bits, so the whole passes below and the nodes of a graph that somebody
+// watches both take it from here.  aligned: every buffer starts at a multiple
+// of its cells' size.
+std::vector<Pass1D> parts_forms(const hx_partitioned_desc* d, int depth, bool aligned) {
+    const int dt = d->dtype == HX_F64 ? 1 : 0;
+    const int vn = dt ? 2 : 4;
+    const bool choose = !d->cells_per_lane && !d->waves_per_group;
+    std::vector<Pass1D> forms;
+    for (int p0 = 0; p0 < d->parts; p0 += kMaxParts) {
+        Pass1D how{};
+        how.g.cpl = d->cells_per_lane ? d->cells_per_lane : 32;
+        how.g.wpg = d->waves_per_group ? d->waves_per_group : 4;
+        how.g.steps = depth;
+        how.g.halo = std::max(vn, (depth + vn - 1) / vn * vn);
+        Geom1D tg;
+        if (choose && tuned_geom_1d(tune_key_1d(d->dtype, d->sizes[p0], depth, true), &tg) &&
+            depth <= max_time_block_1d(d->dtype, tg.cpl)) {
+            how.g.cpl = tg.cpl;
+            how.g.wpg = tg.wpg;
+        } else if (choose && depth <= max_time_block_1d(d->dtype, 16)) {
+            how = choose_pass1d(dt, d->r, d->sizes + p0, std::min(kMaxParts, d->parts - p0), depth,
+                                true);
+            how.prop = how.prop && aligned;
+        }
+        forms.push_back(how);
+    }
+    return forms;
+}
+
 // HX_PART_GRAPH over 1D partitions when nobody can see the nodes (no node
 // events, no hazard checker, no injected failure, no capture): every pass is
 // one launch per group of up to kMaxParts partitions, a node per launch,
 // depending on every node of the previous pass.  What it saves is the host work
 // of a node per partition (about 11 us each, more than most partitions'
-// kernels).  The same arithmetic as the node form, so the same bits, unless a
-// f32 pass takes the propagator form (agreement to rounding).
+// kernels).  The same arithmetic as the node form, so the same bits.
 hx_status run_parts_set(Ctx* c, const hx_partitioned_desc* d, int D, hx_event gate, hx_event* out,
                         int* final_in_b) {
     const int P = d->parts;
     const int dt = d->dtype == HX_F64 ? 1 : 0;
     const int64_t es = dt ? 8 : 4;
-    const int vn = dt ? 2 : 4;
-    const bool choose = !d->cells_per_lane && !d->waves_per_group;
     Geom1D g{};
     g.cpl = d->cells_per_lane ? d->cells_per_lane : 32;
     g.wpg = d->waves_per_group ? d->waves_per_group : 4;
@@ -238,6 +266,7 @@ hx_status run_parts_set(Ctx* c, const hx_partitioned_desc* d, int D, hx_event ga
     // addresses and ranges of both buffer sets
     std::vector<char*> ptr[2];
     std::vector<Access> acc[2];
+    bool aligned = true;
     for (int set = 0; set < 2; ++set)
         for (int p = 0; p < P; ++p) {
             char* q = nullptr;
@@ -247,6 +276,7 @@ hx_status run_parts_set(Ctx* c, const hx_partitioned_desc* d, int D, hx_event ga
             if (s) return s;
             ptr[set].push_back(q);
             acc[set].push_back(a);
+            aligned = aligned && (uintptr_t)q % es == 0;
         }
     for (int p = 0; p < P; ++p)
         if (acc[0][p].buf_slot == acc[1][p].buf_slot)
@@ -264,10 +294,12 @@ hx_status run_parts_set(Ctx* c, const hx_partitioned_desc* d, int D, hx_event ga
         v.clear();
     };
     int left = d->steps;
+    std::vector<Pass1D> forms;
     for (int b = 0; b < passes; ++b) {
         const int depth = std::min(D, left);
         const int src = b % 2;
         left -= depth;
+        if (b == 0 || depth < D) forms = parts_forms(d, depth, aligned);
         for (int p0 = 0; p0 < P; p0 += kMaxParts) {
             const int count = std::min(kMaxParts, P - p0), p1 = p0 + count;
             PartSet1D set{};
@@ -291,20 +323,7 @@ hx_status run_parts_set(Ctx* c, const hx_partitioned_desc* d, int D, hx_event ga
             }
             set.r = d->r;
             set.count = count;
-            Pass1D how{};
-            how.g = g;
-            how.g.steps = depth;
-            how.g.halo = std::max(vn, (depth + vn - 1) / vn * vn);
-            Geom1D tg;
-            if (choose && tuned_geom_1d(tune_key_1d(d->dtype, d->sizes[p0], depth, true), &tg) &&
-                depth <= max_time_block_1d(d->dtype, tg.cpl)) {
-                how.g.cpl = tg.cpl;
-                how.g.wpg = tg.wpg;
-            } else if (choose && depth <= max_time_block_1d(d->dtype, 16)) {
-                how = choose_pass1d(dt, d->r, d->sizes + p0, count, depth, true);
-                for (int k = 0; k < count; ++k)
-                    if (((uintptr_t)set.in[k] | (uintptr_t)set.out[k]) % es) how.prop = false;
-            }
+            const Pass1D& how = forms[p0 / kMaxParts];
             hx_event ev = 0;
             hx_status s = c->submit(
                 SC_COMPUTE, prev.data(), (int)prev.size(), use,
@@ -400,11 +419,20 @@ extern "C" hx_status hx_run_partitioned(hx_ctx ctx, const hx_partitioned_desc* d
         release_locked(c, gate);
         return st;
     };
+    // (a lone partition without neighbours is an ordinary run)
+    const bool whole = !plain && d->dims != 2 && (P > 1 || d->periodic);
+    bool aligned = true;
+    for (int p = 0; p < P && whole; ++p)
+        for (hx_buffer h : {d->bufs_a[p], d->bufs_b[p]})
+            if (const Buffer* q = c->get_buffer(h))
+                aligned = aligned && (uintptr_t)q->ptr % es == 0;
+    std::vector<Pass1D> forms;
     int left = d->steps;
     int node = 0;
     for (int b = 0; b < passes; ++b) {
         const int steps_b = std::min(D, left);
         const bool src_a = (b % 2 == 0);
+        if (whole && (b == 0 || steps_b < D)) forms = parts_forms(d, steps_b, aligned);
         for (int p = 0; p < P; ++p) {
             const int lp = (p + P - 1) % P, rp = (p + 1) % P;
             hx_stencil_args a{};
@@ -433,7 +461,8 @@ extern "C" hx_status hx_run_partitioned(hx_ctx ctx, const hx_partitioned_desc* d
                 if (has_hi) dv[nd++] = prev[rp];
             }
             hx_event ev = 0;
-            s = launch_stencil_locked(c, &a, dv, nd, &ev);
+            s = launch_stencil_locked(c, &a, dv, nd, &ev,
+                                      whole ? &forms[p / kMaxParts] : nullptr);
             if (s) return cleanup(s);
             cur[p] = ev;
             if (plain) chain = ev;

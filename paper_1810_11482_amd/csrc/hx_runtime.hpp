@@ -192,9 +192,12 @@ struct Ctx {
     Plan* get_plan(hx_plan h, int type);
 };
 
-// hx_launch_stencil with the context lock already held.
+struct Pass1D;  // hx_internal.h
+
+// hx_launch_stencil with the context lock already held.  form: a 1D node's pass
+// in the form that its whole pass takes (null: the launch's own choice).
 hx_status launch_stencil_locked(Ctx* c, const hx_stencil_args* a, const hx_event* deps, int ndeps,
-                                hx_event* out);
+                                hx_event* out, const Pass1D* form = nullptr);
 hx_status copy_async_locked(Ctx* c, const hx_copy_desc* d, const hx_event* deps, int ndeps,
                             hx_event* out);
 hx_status when_all_locked(Ctx* c, const hx_event* evs, int n, hx_event* out);

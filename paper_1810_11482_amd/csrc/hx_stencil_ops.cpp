@@ -42,7 +42,7 @@ static hipError_t launch_prop_pass(const Seg1D& s, const PropLine& pl, hipStream
 }
 
 static hx_status launch_1d(Ctx* c, const hx_stencil_args* a, const hx_event* deps, int ndeps,
-                           hx_event* out) {
+                           hx_event* out, const Pass1D* form) {
     const int dt = a->dtype;
     const size_t es = esize(dt);
     const int64_t n = a->nx;
@@ -145,7 +145,13 @@ static hx_status launch_1d(Ctx* c, const hx_stencil_args* a, const hx_event* dep
         Step ps{g, -1};
         ps.g.steps = d;
         ps.g.halo = std::max(vn, round_up(d, vn));
-        if (choose && d <= max_time_block_1d(dt, 16)) {
+        if (form && form->prop) {
+            ps.prop = (int)props.size();
+            props.push_back(form->pl);
+        } else if (form && choose && d <= max_time_block_1d(dt, 16)) {
+            double us;
+            ps.g = choose_geom1d(dt, &n, 1, d, &us);
+        } else if (choose && d <= max_time_block_1d(dt, 16)) {
             const Pass1D c1 = choose_pass1d(dt, a->r, &n, 1, d, ghost);
             ps.g = c1.g;
             if (c1.prop && cell_aligned) {
@@ -314,12 +320,12 @@ static hx_status launch_2d(Ctx* c, const hx_stencil_args* a, const hx_event* dep
 using namespace hx;
 
 hx_status hx::launch_stencil_locked(Ctx* c, const hx_stencil_args* a, const hx_event* deps,
-                                   int ndeps, hx_event* out) {
+                                   int ndeps, hx_event* out, const Pass1D* form) {
     if (!a || !out) return c->fail(HX_ERR_ARG, "null argument");
     if (c->host_only) return c->fail(HX_ERR_NO_DEVICE, "host-only context");
     if (a->dtype != HX_F32 && a->dtype != HX_F64) return c->fail(HX_ERR_ARG, "bad dtype");
     hipSetDevice(c->device);
-    if (a->dims == 1) return launch_1d(c, a, deps, ndeps, out);
+    if (a->dims == 1) return launch_1d(c, a, deps, ndeps, out, form);
     if (a->dims == 2) return launch_2d(c, a, deps, ndeps, out);
     return c->fail(HX_ERR_ARG, "dims must be 1 or 2");
 }
