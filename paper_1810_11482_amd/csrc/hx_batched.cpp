@@ -144,7 +144,7 @@ std::vector<LineSeg> line_segments(const std::vector<Seg1D>& segs, int D, double
                              reinterpret_cast<uintptr_t>(s.halo_lo) |
                              reinterpret_cast<uintptr_t>(s.halo_hi);
         if (s.n < kPropLineMin || at % 4) return {};
-        const int64_t wg = propline_wgs(s.out, s.n);
+        const int64_t wg = propline_wgs(s.n);
         cells += std::max(s.n, 2048 * wg);
         wgs += wg;
         rmax = std::max(rmax, s.r);
@@ -177,7 +177,7 @@ std::vector<LineSeg> line_segments(const std::vector<Seg1D>& segs, int D, double
             q.hi = s.bc_hi == HX_BC_PERIODIC ? q.in : static_cast<const float*>(s.halo_hi);
         q.first = first;
         q.pl = by_rate[s.r];
-        first += (uint32_t)propline_wgs(s.out, s.n);
+        first += (uint32_t)propline_wgs(s.n);
         ls.push_back(q);
     }
     return ls;
@@ -521,7 +521,7 @@ extern "C" hx_status hx_plan_create_batched(hx_ctx ctx, const hx_batch_desc* d, 
     } else if (!lsegs.empty()) {
         std::vector<uint32_t> wg;
         for (size_t i = 0; i < lsegs.size(); ++i) {
-            wg.resize(wg.size() + propline_wgs(lsegs[i].out, lsegs[i].n), (uint32_t)i);
+            wg.resize(wg.size() + propline_wgs(lsegs[i].n), (uint32_t)i);
             bp->lcells += lsegs[i].n;
         }
         bp->lwgs = (int64_t)wg.size();

@@ -131,8 +131,8 @@ hipError_t launch_propline(const PartSet1D& set, const PropLine& pl, hipStream_t
 
 // The same pass over a batch of segments of their own sizes, rates and ends,
 // described in device memory with `nwg` workgroups: workgroup w takes cells
-// 4096 (w - first) .. of segment wg_seg[w] (propline_wgs workgroups each, from
-// a 128-byte line of `out` on).  Every segment's H is `H`.
+// 4096 (w - first) .. of segment wg_seg[w] (propline_wgs workgroups each).
+// Every segment's H is `H`.
 struct LineSeg {
     const float* in;
     float* out;
@@ -143,9 +143,7 @@ struct LineSeg {
     uint32_t first;   // workgroups before this segment's
     PropLine pl;
 };
-inline int64_t propline_wgs(const void* out, int64_t n) {
-    return (n + ((reinterpret_cast<uintptr_t>(out) >> 2) & 31) + 4095) / 4096;
-}
+inline int64_t propline_wgs(int64_t n) { return (n + 4095) / 4096; }
 hipError_t launch_propline_batch(const LineSeg* segs_dev, const uint32_t* wg_seg_dev, int64_t nwg,
                                  int64_t cells, int H, hipStream_t stream);
 
