@@ -32,9 +32,10 @@
 // latency for short ones.  Measured, a pass of 20 / 50 / 200 steps: 2^20 cells
 // 5.3 / 5.6 / 6.5 us, 2^22 9.1 / 9.7 / 10.7 us, 2^24 26 / 27 / 33 us, 2^26
 // 98 / 104 / 134 us (5.5 / 5.2 / 4.0 TB/s); the direct form needs 110 us for
-// 200 steps of 12345679 cells, this one 26 us.  At most 85 VGPRs (6 waves per
-// SIMD; the stepping path spills 44, which the others do not touch): with 128
-// (4 waves) 2^24 cells and 50 steps took 12 % longer.
+// 200 steps of 12345679 cells, this one 26 us.  80 VGPRs (6 waves per
+// SIMD; the stepping path spills 32 to 34, the others none: one value spilled
+// ahead of the products and reloaded among them cost a batch of 622 million
+// cells 8 %): with 128 (4 waves) 2^24 cells and 50 steps took 12 % longer.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -174,6 +175,14 @@ __device__ __forceinline__ f32x4 line_cells4(const Part& s, int64_t c, bool insi
     return v;
 }
 
+// This lane's number, worked out where it is asked for (opaque to the compiler,
+// which otherwise keeps what follows from it in registers across the kernel).
+__device__ __forceinline__ int lane_here() {
+    int l = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    asm volatile("" : "+v"(l));
+    return l;
+}
+
 __device__ __forceinline__ float far4(const f32x4& x) {
     float m = 0.f;
 #pragma unroll
@@ -188,7 +197,7 @@ __device__ __forceinline__ float far4(const f32x4& x) {
 // cells, would be NaN beside an infinity).
 __device__ __forceinline__ void step_line(const Part& s, const PropLine& pl, int64_t c0) {
     constexpr int K = 24;
-    const int l = threadIdx.x & 63;
+    const int l = lane_here();
     const int64_t b = c0 - kReach + (int64_t)K * l;
     float a[K];
     // the lane's cells from `lo` on and before `hi` lie inside the line (32-bit
@@ -234,7 +243,7 @@ __device__ __forceinline__ void line_blocks(const Part& s, const PropLine& a, ui
     char* const tl = lds_all + 4 * 2 * kPlane;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     char* const lds = lds_all + wv * 2 * kPlane;
-    const int l = threadIdx.x & 63, i = l & 31, g = l >> 5;
+    const int l = threadIdx.x & 63;
     const int64_t c0 = 1024 * (4 * (int64_t)wg + wv);
     const bool live = c0 < s.n;
     const bool inside = c0 >= kEdge && c0 + 1024 + kEdge <= s.n;
@@ -328,6 +337,7 @@ __device__ __forceinline__ void line_blocks(const Part& s, const PropLine& a, ui
     // 50 steps of noise at r = 1/4; all in one sum 8.8e-8, stepping 8.3e-8).
     // Narrow windows serve shallow passes, whose stepped error is smaller, and
     // take the product of the two lower halves too.
+    const int ln = lane_here(), i = ln & 31, g = ln >> 5;
     const int d0 = 8 * g + 31 - i;
     const char* ta = tl + 16 * ((d0 & 7) * U + (d0 >> 3));
     f32x16 acc = {}, low = {};
@@ -398,8 +408,8 @@ __device__ __forceinline__ void line_blocks(const Part& s, const PropLine& a, ui
     f32x4 o[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-        o[j] = *reinterpret_cast<const f32x4*>(lds + tpos(8 * j + (l >> 3), l & 7));
-    const int64_t oc = c0 + 4 * l;
+        o[j] = *reinterpret_cast<const f32x4*>(lds + tpos(8 * j + (ln >> 3), ln & 7));
+    const int64_t oc = c0 + 4 * ln;
     if (c0 + 1024 <= s.n) {
         typedef __attribute__((address_space(1))) f32x4u GO;
 #pragma unroll
