@@ -135,36 +135,49 @@ static hx_status launch_1d(Ctx* c, const hx_stencil_args* a, const hx_event* dep
     const int vn = vec_cells(dt);
     const bool cell_aligned = (((uintptr_t)pin | (uintptr_t)pout | (uintptr_t)ptmp |
                                 (uintptr_t)plo | (uintptr_t)phi) & (es - 1)) == 0;
+    // the plan's depths are few (most plans have two), a propagator's taps cost
+    // the host up to 5 us: worked out once per depth
     struct Step {
+        int depth;
         Geom1D g;
         int prop;  // index into props, or -1
     };
-    std::vector<Step> how;
+    std::vector<Step> forms;
     std::vector<PropLine> props;
+    std::vector<int> how;  // each pass's index into forms
     for (int d : plan) {
-        Step ps{g, -1};
+        int k = 0;
+        while (k < (int)forms.size() && forms[k].depth != d) ++k;
+        how.push_back(k);
+        if (k < (int)forms.size()) continue;
+        Step ps{d, g, -1};
         ps.g.steps = d;
         ps.g.halo = std::max(vn, round_up(d, vn));
+        const PropLine* pl = nullptr;
+        Pass1D own{};
         if (form && form->prop) {
-            ps.prop = (int)props.size();
-            props.push_back(form->pl);
-        } else if (form && choose && d <= max_time_block_1d(dt, 16)) {
-            double us;
-            ps.g = choose_geom1d(dt, &n, 1, d, &us);
+            pl = &form->pl;
         } else if (choose && d <= max_time_block_1d(dt, 16)) {
-            const Pass1D c1 = choose_pass1d(dt, a->r, &n, 1, d, ghost);
-            ps.g = c1.g;
-            if (c1.prop && cell_aligned) {
-                ps.prop = (int)props.size();
-                props.push_back(c1.pl);
+            if (form) {
+                double us;
+                own.g = choose_geom1d(dt, &n, 1, d, &us);
+            } else {
+                own = choose_pass1d(dt, a->r, &n, 1, d, ghost);
             }
+            ps.g = own.g;
+            if (own.prop && cell_aligned) pl = &own.pl;
         }
-        how.push_back(ps);
+        if (pl) {
+            ps.prop = (int)props.size();
+            props.push_back(*pl);
+        }
+        forms.push_back(ps);
     }
     std::string what = "stencil1d n=" + std::to_string(n) + " steps=" + std::to_string(a->steps);
     return c->submit(
         SC_COMPUTE, deps, ndeps, acc, what,
-        [=, how = std::move(how), props = std::move(props)](hipStream_t st) -> hipError_t {
+        [=, how = std::move(how), forms = std::move(forms),
+         props = std::move(props)](hipStream_t st) -> hipError_t {
             // passes ping-pong so that the last one lands in out
             const char* src = pin;
             for (int p = 0; p < passes; ++p) {
@@ -172,8 +185,9 @@ static hx_status launch_1d(Ctx* c, const hx_stencil_args* a, const hx_event* dep
                 Seg1D sg = seg;
                 sg.in = src;
                 sg.out = dst;
-                hipError_t e = how[p].prop >= 0 ? launch_prop_pass(sg, props[how[p].prop], st)
-                                                : launch_stencil1d(dt, sg, how[p].g, st);
+                const Step& f = forms[how[p]];
+                hipError_t e = f.prop >= 0 ? launch_prop_pass(sg, props[f.prop], st)
+                                           : launch_stencil1d(dt, sg, f.g, st);
                 if (e != hipSuccess) return e;
                 src = dst;
             }
