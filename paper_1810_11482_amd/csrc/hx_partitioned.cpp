@@ -243,6 +243,61 @@ std::vector<Pass1D> parts_forms(const hx_partitioned_desc* d, int depth, bool al
     return forms;
 }
 
+// The form and geometry of a node's pass over one of them, in a partition of n
+// cells fed by its neighbours.  group: the whole pass's (null: a node between its
+// copies, which hide the kernel's time: up to 50 steps 32 cells per lane,
+// whose few workgroups leave the copies alone.  38 partitions of 121619 cells,
+// 48 steps: 1791 to 1806 us against 1800 to 1828 with the geometry of the
+// shortest kernel; 20 of 209715, 30 steps: 1152 to 1168 against 1160 to 1178).
+Pass1D node_form(const hx_partitioned_desc* d, int64_t n, int depth, const Pass1D* group) {
+    if (group && group->prop) return *group;
+    const int dt = d->dtype == HX_F64 ? 1 : 0;
+    const int vn = dt ? 2 : 4;
+    Pass1D f{};
+    f.g = Geom1D{32, depth, std::max(vn, (depth + vn - 1) / vn * vn), 4};
+    Geom1D tg;
+    if (tuned_geom_1d(tune_key_1d(d->dtype, n, depth, true), &tg) &&
+        depth <= max_time_block_1d(d->dtype, tg.cpl)) {
+        f.g.cpl = tg.cpl;
+        f.g.wpg = tg.wpg;
+    } else if (depth <= max_time_block_1d(d->dtype, 16)) {
+        double us;
+        if (group) {
+            f.g = choose_geom1d(dt, &n, 1, depth, &us);
+        } else {
+            const Geom1D wide = f.g;
+            f = choose_pass1d(dt, d->r, &n, 1, depth, true);
+            if (depth <= 50) f.g = wide;
+        }
+    }
+    return f;
+}
+
+// node_form of the partitions one after another; partitions of one size (most
+// differ by a cell at most) share it.
+class NodeForms {
+public:
+    const Pass1D* of(const hx_partitioned_desc* d, int64_t n, int depth, const Pass1D* group) {
+        for (Entry& e : seen_)
+            if (e.n == n && e.depth == depth && e.group == group) return &e.form;
+        seen_[next_] = Entry{n, depth, group, node_form(d, n, depth, group)};
+        const Pass1D* f = &seen_[next_].form;
+        next_ = (next_ + 1) % 2;
+        return f;
+    }
+    void clear() { seen_[0].n = seen_[1].n = 0; }
+
+private:
+    struct Entry {
+        int64_t n = 0;
+        int depth = 0;
+        const Pass1D* group = nullptr;
+        Pass1D form{};
+    };
+    Entry seen_[2];
+    int next_ = 0;
+};
+
 // HX_PART_GRAPH over 1D partitions when nobody can see the nodes (no node
 // events, no hazard checker, no injected failure, no capture): every pass is
 // one launch per group of up to kMaxParts partitions, a node per launch,
@@ -419,20 +474,26 @@ extern "C" hx_status hx_run_partitioned(hx_ctx ctx, const hx_partitioned_desc* d
         release_locked(c, gate);
         return st;
     };
-    // (a lone partition without neighbours is an ordinary run)
-    const bool whole = !plain && d->dims != 2 && (P > 1 || d->periodic);
+    // (a lone partition without neighbours is an ordinary run, and a given
+    // geometry settles the form)
+    const bool whole = !plain && d->dims != 2 && (P > 1 || d->periodic) && !d->cells_per_lane &&
+                       !d->waves_per_group;
     bool aligned = true;
     for (int p = 0; p < P && whole; ++p)
         for (hx_buffer h : {d->bufs_a[p], d->bufs_b[p]})
             if (const Buffer* q = c->get_buffer(h))
                 aligned = aligned && (uintptr_t)q->ptr % es == 0;
     std::vector<Pass1D> forms;
+    NodeForms node_forms;
     int left = d->steps;
     int node = 0;
     for (int b = 0; b < passes; ++b) {
         const int steps_b = std::min(D, left);
         const bool src_a = (b % 2 == 0);
-        if (whole && (b == 0 || steps_b < D)) forms = parts_forms(d, steps_b, aligned);
+        if (whole && (b == 0 || steps_b < D)) {
+            forms = parts_forms(d, steps_b, aligned);
+            node_forms.clear();
+        }
         for (int p = 0; p < P; ++p) {
             const int lp = (p + P - 1) % P, rp = (p + 1) % P;
             hx_stencil_args a{};
@@ -461,8 +522,9 @@ extern "C" hx_status hx_run_partitioned(hx_ctx ctx, const hx_partitioned_desc* d
                 if (has_hi) dv[nd++] = prev[rp];
             }
             hx_event ev = 0;
-            s = launch_stencil_locked(c, &a, dv, nd, &ev,
-                                      whole ? &forms[p / kMaxParts] : nullptr);
+            const Pass1D* form = nullptr;
+            if (whole) form = node_forms.of(d, d->sizes[p], steps_b, &forms[p / kMaxParts]);
+            s = launch_stencil_locked(c, &a, dv, nd, &ev, form);
             if (s) return cleanup(s);
             cur[p] = ev;
             if (plain) chain = ev;
@@ -545,6 +607,11 @@ extern "C" hx_status hx_run_pipeline(hx_ctx ctx, const hx_pipeline_desc* pd, con
     //    issued in the order they can start: partition 0 of a periodic array
     //    needs the last copy in, so it goes last and blocks no stream meanwhile.
     const bool wrap = d->periodic && P > 1 && T > 0;
+    bool aligned = d->dims != 2 && T > 0 && !d->cells_per_lane && !d->waves_per_group;
+    for (int p = 0; p < P && aligned; ++p)
+        for (hx_buffer h : {d->bufs_a[p], d->bufs_b[p]})
+            if (const Buffer* q = c->get_buffer(h)) aligned = (uintptr_t)q->ptr % es == 0;
+    NodeForms node_forms;
     for (int q = 0; q < P; ++q) {
         const int p = wrap ? (q + 1) % P : q;
         const int lp = (p + P - 1) % P, rp = (p + 1) % P;
@@ -567,7 +634,9 @@ extern "C" hx_status hx_run_pipeline(hx_ctx ctx, const hx_pipeline_desc* pd, con
         dv[nd++] = ein[p];
         if (halo && has_lo) dv[nd++] = ein[lp];
         if (halo && has_hi && rp != lp) dv[nd++] = ein[rp];
-        s = launch_stencil_locked(c, &a, dv, nd, &ek[p]);
+        const Pass1D* form = nullptr;
+        if (aligned && (has_lo || has_hi)) form = node_forms.of(d, d->sizes[p], T, nullptr);
+        s = launch_stencil_locked(c, &a, dv, nd, &ek[p], form);
         if (s) return unwind(s);
         record(P + p, ek[p]);
     }

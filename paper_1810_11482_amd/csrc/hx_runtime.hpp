@@ -194,8 +194,9 @@ struct Ctx {
 
 struct Pass1D;  // hx_internal.h
 
-// hx_launch_stencil with the context lock already held.  form: a 1D node's pass
-// in the form that its whole pass takes (null: the launch's own choice).
+// hx_launch_stencil with the context lock already held.  form: the form and
+// geometry of a 1D halo-fed pass, settled by the caller (null: the launch's own
+// choice, which is also what any geometry given in the arguments calls for).
 hx_status launch_stencil_locked(Ctx* c, const hx_stencil_args* a, const hx_event* deps, int ndeps,
                                 hx_event* out, const Pass1D* form = nullptr);
 hx_status copy_async_locked(Ctx* c, const hx_copy_desc* d, const hx_event* deps, int ndeps,

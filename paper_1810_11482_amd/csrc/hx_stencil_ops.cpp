@@ -66,9 +66,8 @@ static hx_status launch_1d(Ctx* c, const hx_stencil_args* a, const hx_event* dep
     acc.push_back(ac);
 
     Geom1D g;
-    TuneKey key = tune_key_1d(dt, n, a->steps, ghost);
-    Geom1D def{};
-    const bool tuned = tuned_geom_1d(key, &def);
+    Geom1D def{32, 50, 0, 4};
+    const bool tuned = !form && tuned_geom_1d(tune_key_1d(dt, n, a->steps, ghost), &def);
     // the library's own geometry of each pass, unless some of it is given or
     // tuned
     const bool choose = !tuned && !a->cells_per_lane && !a->waves_per_group;
@@ -105,14 +104,9 @@ static hx_status launch_1d(Ctx* c, const hx_stencil_args* a, const hx_event* dep
         return c->fail(HX_ERR_ARG, "time block " + std::to_string(D) + " exceeds the tile limit " +
                                        std::to_string(maxd) + " for cells_per_lane " +
                                        std::to_string(g.cpl));
-    std::vector<int> plan;  // fused depth of each pass
-    for (int left = a->steps; left > 0; left -= std::min(D, left)) plan.push_back(std::min(D, left));
-    if (plan.empty()) plan.push_back(0);
     // (a run of more than one pass of time_block steps, or of 50, needs tmp
     // whatever depths are chosen)
-    const bool need_tmp = plan.size() > 1;
-    if (choose && !a->time_block && need_tmp) plan = choose_depths1d(dt, a->r, n, a->steps);
-    const int passes = (int)plan.size();
+    const bool need_tmp = a->steps > D;
     if (need_tmp) {
         if (a->tmp == 0)
             return c->fail(HX_ERR_ARG, "a run of more than one pass needs a tmp buffer");
@@ -135,8 +129,46 @@ static hx_status launch_1d(Ctx* c, const hx_stencil_args* a, const hx_event* dep
     const int vn = vec_cells(dt);
     const bool cell_aligned = (((uintptr_t)pin | (uintptr_t)pout | (uintptr_t)ptmp |
                                 (uintptr_t)plo | (uintptr_t)phi) & (es - 1)) == 0;
-    // the plan's depths are few (most plans have two), a propagator's taps cost
-    // the host up to 5 us: worked out once per depth
+    // The pass of d steps: its geometry, or true and the propagator's taps.
+    auto pass_form = [&](int d, Geom1D* pg, PropLine* pl) {
+        *pg = g;
+        pg->steps = d;
+        pg->halo = std::max(vn, round_up(d, vn));
+        if (form) {
+            if (form->prop) *pl = form->pl;
+            else *pg = form->g;
+            return form->prop;
+        }
+        if (!choose || d > max_time_block_1d(dt, 16)) return false;
+        const Pass1D own = choose_pass1d(dt, a->r, &n, 1, d, ghost);
+        *pg = own.g;
+        if (own.prop && cell_aligned) *pl = own.pl;
+        return own.prop && cell_aligned;
+    };
+    std::string what = "stencil1d n=" + std::to_string(n) + " steps=" + std::to_string(a->steps);
+    if (!need_tmp) {
+        // one pass, a node of a graph above all: what its launch needs and no
+        // more (a few tenths of a microsecond of the node's host time)
+        seg.in = pin;
+        seg.out = pout;
+        Geom1D pg;
+        PropLine pl;
+        if (pass_form(a->steps, &pg, &pl))
+            return c->submit(SC_COMPUTE, deps, ndeps, acc, what,
+                             [seg, pl](hipStream_t st) { return launch_prop_pass(seg, pl, st); },
+                             out);
+        return c->submit(SC_COMPUTE, deps, ndeps, acc, what,
+                         [seg, pg, dt](hipStream_t st) { return launch_stencil1d(dt, seg, pg, st); },
+                         out);
+    }
+    std::vector<int> plan;  // fused depth of each pass
+    if (choose && !a->time_block)
+        plan = choose_depths1d(dt, a->r, n, a->steps);
+    else
+        for (int left = a->steps; left > 0; left -= std::min(D, left))
+            plan.push_back(std::min(D, left));
+    // its depths are few (most plans have two), and a propagator's taps cost the
+    // host up to 5 us: worked out once per depth
     struct Step {
         int depth;
         Geom1D g;
@@ -151,35 +183,20 @@ static hx_status launch_1d(Ctx* c, const hx_stencil_args* a, const hx_event* dep
         how.push_back(k);
         if (k < (int)forms.size()) continue;
         Step ps{d, g, -1};
-        ps.g.steps = d;
-        ps.g.halo = std::max(vn, round_up(d, vn));
-        const PropLine* pl = nullptr;
-        Pass1D own{};
-        if (form && form->prop) {
-            pl = &form->pl;
-        } else if (choose && d <= max_time_block_1d(dt, 16)) {
-            if (form) {
-                double us;
-                own.g = choose_geom1d(dt, &n, 1, d, &us);
-            } else {
-                own = choose_pass1d(dt, a->r, &n, 1, d, ghost);
-            }
-            ps.g = own.g;
-            if (own.prop && cell_aligned) pl = &own.pl;
-        }
-        if (pl) {
+        PropLine pl;
+        if (pass_form(d, &ps.g, &pl)) {
             ps.prop = (int)props.size();
-            props.push_back(*pl);
+            props.push_back(pl);
         }
         forms.push_back(ps);
     }
-    std::string what = "stencil1d n=" + std::to_string(n) + " steps=" + std::to_string(a->steps);
     return c->submit(
         SC_COMPUTE, deps, ndeps, acc, what,
         [=, how = std::move(how), forms = std::move(forms),
          props = std::move(props)](hipStream_t st) -> hipError_t {
             // passes ping-pong so that the last one lands in out
             const char* src = pin;
+            const int passes = (int)how.size();
             for (int p = 0; p < passes; ++p) {
                 char* dst = ((passes - 1 - p) % 2 == 0) ? pout : ptmp;
                 Seg1D sg = seg;
