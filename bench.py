@@ -644,15 +644,15 @@ def batched_leg(hx, ctx, reps=5):
 
     # the project's autotuner picks the pass depth (20 steps in one pass, or
     # several passes ping-ponging between two buffers), the form and the tile
-    # geometry, timing each candidate on the GPU
+    # geometry, timing each candidate on the GPU; its answer is the fastest plan
+    # that can be named, and a plan that names nothing takes the library's own
+    # choice where the tuner timed that as faster still
     t0 = time.perf_counter()
     tb_ = hx.hx_tune_batched(ctx, hx.HX_F32, spec.steps, segs, 4000)
     tune_s = time.perf_counter() - t0
     D = tb_.steps
     passes = spec.steps // D
-    kw = dict(cells_per_lane=tb_.cells_per_lane, waves_per_group=tb_.waves_per_group,
-              grid_waves_per_cu=tb_.grid_waves_per_cu, form=tb_.form,
-              span_blocks=tb_.span_blocks)
+    kw = dict(form=hx.HX_FORM_AUTO)
     plans = [hx.hx_plan_create_batched(ctx, hx.HX_F32, D, segs, hx.HX_BATCH_PERSISTENT, **kw)]
     if passes > 1:  # the return pass: out -> in
         back = [hx.segment(inp=bufs[1], in_offset=int(o) * 4, out=bufs[0],
@@ -682,10 +682,19 @@ def batched_leg(hx, ctx, reps=5):
     assert hx.hx_wait(ctx, e) == hx.HX_OK, hx.hx_last_error(ctx)
     hx.hx_event_release(ctx, e)
     sec = (time.perf_counter() - t0) / reps
-    tuned = {"tuner": "hx_tune_batched", "tuner_seconds": tune_s, "depth": D, "passes": passes,
+    plan = hx.hx_plan_create_batched(ctx, hx.HX_F32, D, segs, hx.HX_BATCH_PERSISTENT,
+                                     cells_per_lane=tb_.cells_per_lane, form=tb_.form,
+                                     waves_per_group=tb_.waves_per_group,
+                                     grid_waves_per_cu=tb_.grid_waves_per_cu,
+                                     span_blocks=tb_.span_blocks)
+    named = {"ms": timed(plan, reps) * passes * 1e3,
              "form": "propagator" if tb_.form == hx.HX_FORM_PROPAGATOR else "direct",
              "cells_per_lane": tb_.cells_per_lane, "waves_per_group": tb_.waves_per_group,
              "grid_waves_per_cu": tb_.grid_waves_per_cu, "span_blocks": tb_.span_blocks}
+    hx.hx_plan_destroy(ctx, plan)
+    tuned = {"tuner": "hx_tune_batched", "tuner_seconds": tune_s, "depth": D, "passes": passes,
+             "plan": "AUTO, nothing named (the tuner's choice or the library's, by the tuner's "
+                     "timing)", "best_named": named}
     log(f"batched persistent, tuned {tuned}: {sec * 1e3:.3f} ms")
     res["persistent"] = {"ms": sec * 1e3, "cell_updates_per_s": updates / sec,
                          "hbm_algorithmic_GBps": total * 8 * passes / sec / 1e9,
@@ -796,9 +805,12 @@ def pipeline_leg(hx, ctx0, P, T, r, cpl, ref):
     err = {"rel_l2": float(np.linalg.norm(o64 - ref) / np.linalg.norm(ref)),
            "max_rel_per_cell": float(np.max(np.abs(o64 - ref) / np.abs(ref))), "cells": P.n}
     del o64
-    # kernels alone: the single-pass device-resident graph
+    # kernels alone: the single-pass device-resident graph, a kernel per
+    # partition as in the run (without node events it would be one launch)
     P.cur_in_a = True
-    t_kernel, _ = time_steps(P, 3, hx.HX_PART_GRAPH, T, cpl)
+    t_kernel, nodes = time_steps(P, 3, hx.HX_PART_GRAPH, T, cpl, nodes=True)
+    for e in nodes:
+        hx.hx_event_release(ctx, e)
     C = intervals_union([tuple(x) for x in spans["h2d"] + spans["d2h"]])
     K = intervals_union([tuple(x) for x in spans["kernel"]])
     CK = intersect_len(C, K)
@@ -1012,7 +1024,8 @@ def fp64_leg(hx, ctx, reps=10):
 
 def banded2d_leg(hx, ctx):
     """16384^2 fp32, zero-Dirichlet, r = 0.2, 200 steps, 16 row bands with
-    halo-row futures (the per-band future graph), Gaussian-bump field."""
+    halo-row futures, Gaussian-bump field: whole passes, and the future graph of a
+    node per band and pass (node events taken, which keeps its nodes apart)."""
     import torch
     import workloads
     spec = workloads.Banded2D()
@@ -1065,10 +1078,11 @@ def banded2d_leg(hx, ctx):
         for it in range(2):
             torch.cuda.synchronize()
             t0 = time.perf_counter()
-            ev, in_b, _ = hx.hx_run_partitioned(ctx, d)
+            ev, in_b, evs = hx.hx_run_partitioned(ctx, d, node_events=mode == hx.HX_PART_GRAPH)
             assert hx.hx_wait(ctx, ev) == hx.HX_OK, hx.hx_last_error(ctx)
             ts.append(time.perf_counter() - t0)
-            hx.hx_event_release(ctx, ev)
+            for e in [ev] + (evs or []):
+                hx.hx_event_release(ctx, e)
         sec = ts[-1]
         mname = "batched" if mode == hx.HX_PART_BATCHED else "graph"
         log(f"2D bands {mname} tb={tb} cpl={cpl} rows={rows}: {sec * 1e3:.2f} ms")
@@ -1093,9 +1107,10 @@ def banded2d_leg(hx, ctx):
                             periodic=False, time_block=tb, cells_per_lane=cpl, dims=2,
                             nx=spec.nx, rows_per_block=rows, mode=mode)
     upload()
-    ev, in_b, _ = hx.hx_run_partitioned(ctx, d)
+    ev, in_b, evs = hx.hx_run_partitioned(ctx, d, node_events=mode == hx.HX_PART_GRAPH)
     assert hx.hx_wait(ctx, ev) == hx.HX_OK
-    hx.hx_event_release(ctx, ev)
+    for e in [ev] + (evs or []):
+        hx.hx_event_release(ctx, e)
     rng = np.random.default_rng(13)
     pts = [(0, 0), (1023, 5000), (1024, 5000), (spec.ny - 1, spec.nx - 1)] + \
         [(int(a), int(b)) for a, b in zip(rng.integers(0, spec.ny, 6), rng.integers(0, spec.nx, 6))]

@@ -616,7 +616,9 @@ hx_status hx_hazard_report(hx_ctx ctx, char* buf, size_t len);
  * buffers (out and tmp are overwritten) for about `budget_ms` (at least one
  * candidate runs), store the fastest in the process-wide cache under the
  * problem's key (dims, dtype, size class, steps), and return it in *best.
- * Later launches with geometry fields 0 use the cached entry.  Each candidate
+ * Later launches with geometry fields 0 use the cached entry, unless the
+ * library's own choice, timed last, was faster than every geometry that can be
+ * named: then they keep that.  Each candidate
  * runs once to warm up, then three times chained on one stream: in a timing
  * context (hx_ctx_opts.timing) its time is the mean HIP-event span of those
  * launches, otherwise their host time over three. */
@@ -630,9 +632,12 @@ hx_status hx_tune_stencil(hx_ctx ctx, const hx_stencil_args* args, int budget_ms
  * and four waves per group, interleaved, the plan's choice, spans of 128 and
  * 40 blocks; DIRECT over cells per lane 8..64,
  * waves per group 1, 2, 4 and a persistent grid of 16 or 64 waves per CU);
- * a candidate costs T / D times its pass.  *best is the fastest, with
- * best->steps = D: the run is T / D passes of that plan (ping-ponging in and
- * out).  It is cached under the key of T and of D. */
+ * a candidate costs T / D times its pass.  *best is the fastest plan that can be
+ * named, with best->steps = D: the run is T / D passes of that plan (ping-ponging
+ * in and out).  It is cached under the key of T and of D, for plans that name
+ * nothing.  An AUTO plan of T steps that names nothing may be faster than any that
+ * can be named (its line propagator pass has no name): it is timed last, and then
+ * such plans keep the library's own choice and only *best tells of the other. */
 hx_status hx_tune_batched(hx_ctx ctx, const hx_batch_desc* desc, int budget_ms,
                           hx_batch_desc* best);
 
