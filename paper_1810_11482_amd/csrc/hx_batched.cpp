@@ -151,18 +151,18 @@ std::vector<LineSeg> line_segments(const std::vector<Seg1D>& segs, int D, double
     }
     const double us = propline_us(rmax, cells, D, false) + 0.005 * (double)segs.size();
     if (wgs >= (int64_t(1) << 24) || !(us < direct_us)) return {};
-    // the widest window serves all; a rate's taps are computed once
+    // the widest window, the largest rate's, serves all; a rate's taps are
+    // computed once
+    PropLine widest;
+    if (!propline_setup(rmax, D, &widest)) return {};
+    const int H = widest.H;
     std::map<double, PropLine> by_rate;
-    int H = 0;
     for (const Seg1D& s : segs) {
         PropLine& pl = by_rate[s.r];
-        if (pl.D) continue;
-        if (!propline_setup(s.r, D, &pl)) return {};
-        H = std::max(H, pl.H);
+        if (!pl.D && (!propline_setup(s.r, D, &pl, H) || pl.H != H)) return {};
     }
-    for (auto& kv : by_rate)
-        if (kv.second.H != H && !propline_setup(kv.first, D, &kv.second, H)) return {};
     std::vector<LineSeg> ls;
+    ls.reserve(segs.size());
     uint32_t first = 0;
     for (const Seg1D& s : segs) {
         LineSeg q{};
@@ -520,6 +520,7 @@ extern "C" hx_status hx_plan_create_batched(hx_ctx ctx, const hx_batch_desc* d, 
         }
     } else if (!lsegs.empty()) {
         std::vector<uint32_t> wg;
+        wg.reserve((size_t)lsegs.back().first + propline_wgs(lsegs.back().n));
         for (size_t i = 0; i < lsegs.size(); ++i) {
             wg.resize(wg.size() + propline_wgs(lsegs[i].n), (uint32_t)i);
             bp->lcells += lsegs[i].n;

@@ -496,17 +496,17 @@ constexpr int64_t kNtCells = int64_t(1) << 25;
 // of the coefficients of (r/x + a + r x)^D, a = 1 - 2r, whose terms are all
 // positive (no cancellation), normalised to sum 1; K = D, or where the taps
 // have fallen below 1e-40 of the largest.
-int line_taps(double r, int D, std::vector<double>& p) {
+int line_taps(double r, int D, double (&p)[kReach + 2]) {
     const double sigma = std::sqrt(2.0 * r * D);
     const int K = std::min(D, (int)(14.0 * sigma) + 20);
-    p.assign(K + 2, 0.0);
+    p[K + 1] = 0.0;
     p[K] = 1e-280;
     const double q = (1.0 - 2.0 * r) / r;
     for (int j = K; j >= 1; --j)
         p[j - 1] = ((D + j + 1) * p[j + 1] + q * j * p[j]) / (D - j + 1);
     double sum = p[0];
     for (int j = 1; j <= K; ++j) sum += 2.0 * p[j];
-    for (double& x : p) x /= sum;
+    for (int j = 0; j <= K; ++j) p[j] /= sum;
     return K;
 }
 
@@ -532,7 +532,7 @@ float to_half(float x, uint16_t* h) {
 bool propline_setup(double r, int D, PropLine* out, int min_H) {
     // (up to r = 1/4 the taps fall monotonically from p_0)
     if (!(r >= 1e-3 && r <= 0.25) || D < 1 || D > kReach) return false;
-    std::vector<double> p;
+    double p[kReach + 2];
     const int K = line_taps(r, D, p);
     auto tap = [&](int j) { return std::abs(j) <= K ? p[std::abs(j)] : 0.0; };
     // Everything omitted is kept near the fp16 split's own floors (2^-39 of the
@@ -540,9 +540,10 @@ bool propline_setup(double r, int D, PropLine* out, int min_H) {
     // or smaller fail the check: the zero crossings of a smooth field mostly
     // pass.  The half window: the least multiple of 8 cells whose outer taps
     // sum to less than 2^-39 (all sum to 1), at most 64.
-    std::vector<double> tail(K + 2, 0.0);  // tail[j] = sum of p_k, k >= j
+    double tail[kReach + 2];  // tail[j] = sum of p_k, k >= j
+    tail[K + 1] = 0.0;
     for (int j = K; j >= 0; --j) tail[j] = tail[j + 1] + p[j];
-    auto past = [&](int j) { return j <= K ? tail[std::max(j, 0)] : 0.0; };
+    auto past = [&](int j) { return tail[std::min(std::max(j, 0), K + 1)]; };
     int H = std::max(8, min_H);
     while (H < 64 && 2.0 * past(H + 1) > 1.8e-12) H += 8;
     const int NC = (32 + 2 * H) / 16;
