@@ -901,10 +901,16 @@ __global__ __launch_bounds__(256) void k_vc_adj(VCDev a, UStates us, double* __r
         if constexpr (FOLD) {
             if (rout && ln.own) {
                 double* tp = total + r * nx + xl;
+                // (one branch for the row, not one around each cell's load)
+                double t0[C] = {};
+                if (!a.fresh) {
+#pragma unroll
+                    for (int j = 0; j < C; ++j)
+                        if (!RAG || ln.in[j]) t0[j] = tp[j];
+                }
 #pragma unroll
                 for (int j = 0; j < C; ++j)
-                    if (!RAG || ln.in[j])
-                        tp[j] = (a.fresh ? 0.0 : tp[j]) + (double)gr[m6(P - D)][j];
+                    if (!RAG || ln.in[j]) tp[j] = t0[j] + (double)gr[m6(P - D)][j];
             }
         } else {
             store_lane_if<T, RAG, ST_NT>(rsg, ln, lane_off, rout, r, nx, gr[m6(P - D)]);
