@@ -997,13 +997,18 @@ const void* fused_kernel(int dtype, int64_t nx, bool adjoint, int steps, int var
                       : fused_kernel<double, false>(adjoint, steps, variant);
 }
 
-// Rows per chunk when the caller leaves the choice to the library: enough
-// chunks that strips x chunks waves fill the device's resident wave slots for
-// this kernel once (one round of waves: no partly filled second round), at
-// least 12 - 2D rows (two groups of the six-row loop).  A wave streams its
-// chunk plus 2D halo rows, so taller chunks also recompute fewer rows.  The
-// result does not depend on the chunk height.
-int fill_rows(const void* k, int64_t nstrips, int64_t ny, int depth) {
+// Rows per chunk when the caller leaves the choice to the library.  Large grids:
+// enough chunks that strips x chunks waves fill the device's resident wave slots
+// for this kernel once (one round of waves: no partly filled second round).  A
+// wave streams its chunk plus 2D halo rows, in groups of six, so taller chunks
+// also recompute fewer rows.  Where that gives fewer than 16 rows: 16, or that
+// number or whole groups (6 k - 2D rows, up to 28) if the modelled time, groups
+// x max(1, c w) with w the waves of the fullest SIMD and c 0.6 for float, 0.8 for
+// double, is less than 0.9 of 16 rows'.  Measured, float, four forward steps of
+// 2048^2: 10 rows 21.0 us, 16 rows 24.6, 7 rows (one full round) 26.2; of 1024^2:
+// 4 rows 14.4, 10 rows 15.7, 16 rows 18.3; one step of doubles of 1536^2: 16 rows
+// 25.3, 10 rows 30.4.  The result does not depend on the chunk height.
+int fill_rows(const void* k, int dtype, int64_t nstrips, int64_t ny, int depth) {
     static std::mutex mu;
     static std::vector<std::pair<std::pair<const void*, int>, int64_t>> cache;
     int dev = 0;
@@ -1030,15 +1035,34 @@ int fill_rows(const void* k, int64_t nstrips, int64_t ny, int depth) {
         cache.push_back({{k, dev}, slots});
     }
     const int64_t chunks = std::max<int64_t>(1, slots / nstrips);
-    const int64_t rows = std::max<int64_t>(12 - 2 * depth, (ny + chunks - 1) / chunks);
-    return (int)std::min<int64_t>(rows, int64_t(1) << 30);
+    const int64_t rows = (ny + chunks - 1) / chunks;
+    if (rows >= 16) return (int)std::min<int64_t>(rows, int64_t(1) << 30);
+    const double c = dtype == 0 ? 0.6 : 0.8;
+    auto cost = [&](int64_t r) {
+        const int64_t waves = nstrips * ((ny + r - 1) / r), w = (waves + 1023) / 1024;
+        const int64_t most = std::max<int64_t>(1, slots / 1024);  // of one round
+        const int64_t full = (w - 1) / most;
+        return ((r + 2 * depth + 5) / 6) *
+               (full * std::max(1.0, c * most) + std::max(1.0, c * (w - full * most)));
+    };
+    int best = 16;
+    double least = 0.9 * cost(16);
+    auto consider = [&](int64_t r) {
+        if (cost(r) < least) {
+            best = (int)r;
+            least = cost(r);
+        }
+    };
+    if (rows >= 12 - 2 * depth) consider(rows);
+    for (int r = 12 - 2 * depth; r <= 28; r += 6) consider(r);
+    return best;
 }
 
-hipError_t launch_fused(const void* k, VCDev a, int depth, int rows_req, void* arg3, void* arg4,
+hipError_t launch_fused(const void* k, int dtype, VCDev a, int depth, int rows_req, void* arg3, void* arg4,
                         bool adjoint, hipStream_t st) {
     if (!k) return hipErrorInvalidValue;
     int64_t nstrips = vc_strips(a.nx);
-    a.rows = rows_req > 0 ? rows_req : fill_rows(k, nstrips, a.ny, depth);
+    a.rows = rows_req > 0 ? rows_req : fill_rows(k, dtype, nstrips, a.ny, depth);
     int64_t nwaves = nstrips * ((a.ny + a.rows - 1) / a.rows);
     const int wpg = 4;
     const int64_t groups = (nwaves + wpg - 1) / wpg;
@@ -1057,7 +1081,7 @@ hipError_t launch_vc_forward(int dtype, int steps, const VCArgs& v, hipStream_t 
     VCDev a{v.u, v.kappa, nullptr, v.out, nullptr, v.nx, v.ny, v.dt, 0, 1};
     const int variant = mid ? 1 : 0;
     const void* k = fused_kernel(dtype, v.nx, false, steps, variant);
-    return launch_fused(k, a, steps, v.rows, &mid, &mid_stride, false, st);
+    return launch_fused(k, dtype, a, steps, v.rows, &mid, &mid_stride, false, st);
 }
 
 hipError_t launch_vc_adjoint(int dtype, int steps, const VCArgs& v, const void* const* ustates,
@@ -1072,7 +1096,7 @@ hipError_t launch_vc_adjoint(int dtype, int steps, const VCArgs& v, const void* 
     VCDev a{nullptr, v.kappa, v.lam, v.out, v.gacc, v.nx, v.ny, v.dt, 0, 1, fresh ? 1 : 0};
     const int variant = (zero_in ? 1 : 0) | (fold_total ? 2 : 0);
     const void* k = fused_kernel(dtype, v.nx, true, steps, variant);
-    return launch_fused(k, a, steps, v.rows, &us, &fold_total, true, st);
+    return launch_fused(k, dtype, a, steps, v.rows, &us, &fold_total, true, st);
 }
 
 hipError_t launch_fold(int dtype, void* acc, double* total, int64_t n, hipStream_t st) {
