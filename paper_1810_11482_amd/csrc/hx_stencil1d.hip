@@ -580,6 +580,12 @@ constexpr LineCost kLineCost[2][4] = {
     {{8, 4.77, 0.082, 0.0322, 0.878}, {16, 8.59, 0.098, 0.0614, 1.56},
      {32, 11.7, 0.166, 0.123, 4.15}, {64, 22.3, 0.317, 0.294, 12.2}}};
 constexpr int kLineDepth = 200;  // deepest pass considered (the deepest measured)
+// One or two steps of doubles that outgrow the last-level cache are bound by
+// memory, where the fit says too little: 32 cells per lane.  2^25 cells 98.8 us
+// (16 cells 104.6, 8 cells 99.5), 50000003 145.6 (154.1, 149.4), 2^27 396 (409,
+// 406); 2^24 cells 54.5 (53.0, 51.4), and three steps of 2^25 100.7 (98.0, 95.0).
+// (Runs of 2^20 cells and more on average: short ones would leave lanes idle.)
+constexpr int64_t kWideCells = int64_t(1) << 25;
 
 }  // namespace
 
@@ -590,7 +596,11 @@ Geom1D choose_geom1d(int dtype, const int64_t* n, int count, int depth, double* 
     g.halo = depth > vn ? (depth + vn - 1) / vn * vn : vn;
     g.wpg = 4;
     *us = 0.0;
+    int64_t cells = 0;
+    for (int k = 0; k < count; ++k) cells += n[k];
+    const bool wide = dtype && depth <= 2 && cells >= kWideCells && cells >= (int64_t)count << 20;
     for (const LineCost& c : kLineCost[dtype ? 1 : 0]) {
+        if (wide && c.cpl != 32) continue;
         const int64_t wout = 64LL * c.cpl - 2LL * g.halo;
         if (wout < vn) continue;
         int64_t waves = 0;
