@@ -83,6 +83,9 @@ inline int64_t tiles_1d(const Seg1D& s, const Geom1D& g) {
 // lines lie); *us receives the pass's modelled time.  depth must fit 16 cells
 // per lane.
 Geom1D choose_geom1d(int dtype, const int64_t* n, int count, int depth, double* us);
+// The same model's time at `cpl` cells per lane (infinite where depth does not
+// fit).
+double geom1d_us(int dtype, const int64_t* n, int count, int depth, int cpl);
 // Pass depths of a run of `steps` steps at rate r over n cells, in the
 // library's choice.
 std::vector<int> choose_depths1d(int dtype, double r, int64_t n, int steps);

@@ -589,6 +589,23 @@ constexpr int64_t kWideCells = int64_t(1) << 25;
 
 }  // namespace
 
+static double geom1d_us(const LineCost& c, int vn, const int64_t* n, int count, int depth) {
+    const int halo = depth > vn ? (depth + vn - 1) / vn * vn : vn;
+    const int64_t wout = 64LL * c.cpl - 2LL * halo;
+    if (wout < vn) return std::numeric_limits<double>::infinity();
+    int64_t waves = 0;
+    for (int k = 0; k < count; ++k) waves += (n[k] + wout - 1) / wout;
+    double w = (double)waves / 1024.0;
+    if (w > 1.0 && w < 6.0) w = 0.5 * (w + std::ceil(w - 0.05));
+    return c.a + std::max(depth * c.l, depth * w * c.i + w * c.m);
+}
+
+double geom1d_us(int dtype, const int64_t* n, int count, int depth, int cpl) {
+    for (const LineCost& c : kLineCost[dtype ? 1 : 0])
+        if (c.cpl == cpl) return geom1d_us(c, dtype ? 2 : 4, n, count, depth);
+    return std::numeric_limits<double>::infinity();
+}
+
 Geom1D choose_geom1d(int dtype, const int64_t* n, int count, int depth, double* us) {
     const int vn = dtype ? 2 : 4;
     Geom1D g{};
@@ -601,14 +618,8 @@ Geom1D choose_geom1d(int dtype, const int64_t* n, int count, int depth, double* 
     const bool wide = dtype && depth <= 2 && cells >= kWideCells && cells >= (int64_t)count << 20;
     for (const LineCost& c : kLineCost[dtype ? 1 : 0]) {
         if (wide && c.cpl != 32) continue;
-        const int64_t wout = 64LL * c.cpl - 2LL * g.halo;
-        if (wout < vn) continue;
-        int64_t waves = 0;
-        for (int k = 0; k < count; ++k) waves += (n[k] + wout - 1) / wout;
-        double w = (double)waves / 1024.0;
-        if (w > 1.0 && w < 6.0) w = 0.5 * (w + std::ceil(w - 0.05));
-        const double t = c.a + std::max(depth * c.l, depth * w * c.i + w * c.m);
-        if (*us == 0.0 || t < *us) {
+        const double t = geom1d_us(c, vn, n, count, depth);
+        if (!std::isinf(t) && (*us == 0.0 || t < *us)) {
             *us = t;
             g.cpl = c.cpl;
         }
