@@ -464,9 +464,10 @@ hipError_t launch_vc_step(int dtype, bool adjoint, const VCArgs& v, hipStream_t 
 // (vc_fused_supported), else hipErrorInvalidValue.
 constexpr int kVcFusedMax = 4;
 // The tile form of a pass of up to kVcTileMax steps (hx_vctile.hip; `waves`
-// waves per workgroup: 2 to 16 forward in float, else 2 to 8; 2 steps < 4
-// waves), any grid: forward with mid as launch_vc_forward, adjoint as
-// launch_vc_adjoint.  The same bits.
+// waves per workgroup: 2 to 16 forward in float, else 2 to 8; 2 steps < rows x
+// waves, with 3 rows per wave in the adjoint of doubles and 4 otherwise), any
+// grid: forward with mid as launch_vc_forward, adjoint as launch_vc_adjoint.
+// The same bits.
 constexpr int kVcTileMax = 12;
 hipError_t launch_vc_tile(int dtype, bool adjoint, int steps, int waves, const VCArgs& v,
                           void* mid, int64_t mid_stride, const void* const* ustates, bool zin,

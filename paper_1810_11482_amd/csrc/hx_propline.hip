@@ -19,12 +19,14 @@
 //     fails it.
 //   * A block that fails is stepped in registers (24 cells per lane, the
 //     direct form's arithmetic), 2 instructions per cell and step.
-//   * Boundaries.  Blocks near an end take their cells one by one: from the
-//     neighbour's cells, or, past a zero-Dirichlet end, from the odd
-//     reflection of the line about the ghost cell (u_{-1} = 0, u_{-2-k} =
-//     -u_k), which the steps preserve exactly.
+//   * Boundaries.  Blocks near an end take what lies past it from the
+//     neighbour's cells, or, past a zero-Dirichlet end, from the odd reflection
+//     of the line about the ghost cell (u_{-1} = 0, u_{-2-k} = -u_k), which the
+//     steps preserve exactly: four cells in one load, cell by cell only where
+//     four straddle an end or the far end of a halo (line_cells4).
 //   * Blocks start at the run's first cell whatever its address, so the bits do
-//     not depend on where a run lies in memory.  (Blocks that start where `out`
+//     not depend on where a run lies in memory, nor on who launches the pass (a
+//     node of a graph, or all partitions in one).  (Blocks that start where `out`
 //     is 128-byte aligned store whole lines: 1 to 5 % faster on misaligned runs
 //     of 2^25 cells and more, 820 us against 834 for a batch of 622 million, and
 //     up to 2 % slower on short ones.)

@@ -19,8 +19,10 @@
 // Arithmetic.  For 0 <= r <= 3/8 the tile is advanced in the rescaled form
 // w' = fma(r/(1-2r), l + rt, w) with a periodic rescale (set_rate_1d): one add
 // and one fma per cell-step.  Other rates use s = l + rt; d = fma(-2, c, s);
-// c' = fma(r, d, c).  Either way the result of a pass depends only on its step
-// count, not on the tile geometry.
+// c' = fma(r, d, c).  Either way the result of a pass of this kernel depends
+// only on its step count, not on the tile geometry.  (A float pass that the
+// library takes in the propagator form, hx_propline.hip, agrees to rounding;
+// choose_pass1d draws the line, by size, rate and depth alone.)
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -663,11 +665,12 @@ Pass1D choose_pass1d(int dtype, double r, const int64_t* n, int count, int depth
         cells += n[k];
         least = std::min(least, n[k]);
     }
-    // (a node of a graph of partitions costs the host about 11 us; up to 64
-    // steps the taps and the larger kernel argument add to that what the kernel
-    // saves unless the node is long: 16 nodes of 2^20 cells, 50 steps, between
-    // their copies: 2.31 ms against 2.24.  Below 4096 cells the node's bits
-    // stay those of the whole pass over its array, too)
+    // (a halo-fed launch by itself, a node that a program or a host-to-host run
+    // composes, costs the host about 11 us; up to 64 steps the taps and the larger
+    // kernel argument add to that what the kernel saves unless the node is long.
+    // Measured on one configuration, 16 nodes of 2^20 cells, 50 steps, between
+    // their copies: 2.31 ms against 2.24.  Below 4096 cells such a node's bits
+    // also stay those of an unsplit line of its size)
     const bool node = fed && depth <= 64;
     const int64_t min_n = node ? 4096 : kPropLineMin;
     const double host_us = node && count == 1 ? 8.0 : 0.0;

@@ -26,7 +26,7 @@
 // plus about 5 us per pass to launch, load and store.  Measured per step,
 // pass included: 256^2 float 0.83 us (12.4 us per pass of 15 steps; the
 // streaming form's best 2.2 us), 1024^2 1.04 us (streaming 2.5), 4096^2 5.0 us
-// (6.5), 8192^2 18.0 us (20.0), 16384^2 61.7 us (56.1); 4096^2 double 7.9 us
+// (6.5), 8192^2 18.0 us (20.0), 16384^2 61.7 us (50.3); 4096^2 double 7.9 us
 // (10.7), 16384^2 110 us (118).
 #include <algorithm>
 #include <cmath>
@@ -387,8 +387,9 @@ double tile_us(const TileCost& c, int64_t tiles, int depth) {
 }
 
 // From this many float cells on, the streaming form's smaller redundancy wins at
-// every depth: 10000 x 12000 cells 29.6 us per step against 31.1, 16384^2 55.6
-// against 61.7.
+// every depth: 10000 x 12000 cells 25.8 us per step against 31.1, 16384^2 50.3
+// against 61.7.  (The two sides of the line are modelled apart: here by the times
+// of one aligned grid, without terms for bands or ragged rows.)
 constexpr double kStreamCells = 1.0e8;
 
 constexpr int kTileMax = 24;  // deepest tile pass considered
@@ -434,9 +435,9 @@ Form2D choose_form2d(int dtype, int64_t nx, const int64_t* ny, int n, int depth,
     double cells = 0.0;
     for (int k = 0; k < n; ++k) cells += (double)nx * (double)ny[k];
     if (dtype == 0 && cells >= kStreamCells && stencil2d_supported(dtype, 4, depth)) {
-        // 16384^2: 10 steps 556 us at 56 rows per wave and one wave per
-        // workgroup (561 at 64 and four), 8 steps 486 us at 32 and four, 12
-        // and 16 steps 754 and 1029 us at 96 and one; shallow passes are bound
+        // 16384^2: 10 steps 509 us at 56 rows per wave and one wave per
+        // workgroup (508 at 64 and four), 8 steps 474 us at 32 and four, 12
+        // and 16 steps 628 and 799 us at 96 and one; shallow passes are bound
         // by their bytes, and most waves fetch them fastest
         f.tile = false;
         f.g.rows = depth <= 6 ? 24 : (depth <= 8 ? 32 : (depth == 10 ? 56 : 96));
