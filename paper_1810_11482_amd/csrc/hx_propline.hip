@@ -504,8 +504,14 @@ int line_taps(double r, int D, double (&p)[kReach + 2]) {
     p[K + 1] = 0.0;
     p[K] = 1e-280;
     const double q = (1.0 - 2.0 * r) / r;
-    for (int j = K; j >= 1; --j)
-        p[j - 1] = ((D + j + 1) * p[j + 1] + q * j * p[j]) / (D - j + 1);
+    // (the divisions ahead of the recurrence, out of its chain: a batch of 4096
+    // rates pays for as many)
+    double a[kReach + 2], b[kReach + 2];
+    for (int j = 1; j <= K; ++j) {
+        a[j] = (double)(D + j + 1) / (D - j + 1);
+        b[j] = q * j / (D - j + 1);
+    }
+    for (int j = K; j >= 1; --j) p[j - 1] = a[j] * p[j + 1] + b[j] * p[j];
     double sum = p[0];
     for (int j = 1; j <= K; ++j) sum += 2.0 * p[j];
     for (int j = 0; j <= K; ++j) p[j] /= sum;
@@ -569,7 +575,7 @@ bool propline_setup(double r, int D, PropLine* out, int min_H) {
         return past(0) + past(1) - past(j1 + 1) - past(-j0 + 1);
     };
     double E = 0.0;
-    for (int m = 0; m < 32; ++m) {
+    for (int m = 0; m < 16; ++m) {  // (row 31 - m mirrors row m)
         double e = past(H + m + 1) + past(H + 32 - m);
         for (int c = 0; c < NC; ++c) {
             const uint32_t L = (levels >> (2 * c)) & 3;
